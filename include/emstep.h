@@ -109,8 +109,8 @@ typedef struct {
                                   stream); 0 = plain launches (paper: "Stepping algorithm", the
                                   launch overhead of the outer loop) */
     int32_t lds_tables;        /* 1: each block of the along-step kernels (which run the pre-step)
-                                  and of the drain stages the physics tables in LDS; 0: tables are
-                                  read through the caches */
+                                  stages the physics tables in LDS; 0: tables are read through the
+                                  caches (the block-local step loops always stage them) */
     int32_t streams;           /* 1..4: independent kernels of an iteration (the along-step kernels;
                                   the interaction kernels) run as concurrent branches on up to this
                                   many default-priority streams created by the library (paper:
@@ -385,19 +385,25 @@ ems_status ems_sort_keys_noalloc(ems_ctx* ctx, const uint8_t* keys, uint64_t n, 
  * occupancy; none set: that point's kernels are not launched at all).  The
  * sort policy itself (partition, radix, queue) is one per context.
  *
+ * Block-local step loops: with the policy PARTITION, fuse_interactions and
+ * fuse_along set, one stream, no parent-slot reuse, no deterministic appends
+ * and no profile of another role than vacancies, init or drain, ems_step and
+ * ems_run run their iterations in launches in which every block steps the
+ * tracks of its own slots (ems_step: every live track once per iteration;
+ * ems_run: a block's tracks as its waves get to them), as long as the tables
+ * fit the blocks' LDS.  The sort points, block sizes and graph batches then
+ * play no part.  The results are those of the separate kernels.
+ *
  * Drain (ems_run only; 0 = off): once the latest counter snapshot shows fewer
  * than drain_threshold tracks alive, queued or pending, and no more than the
  * snapshot before it (the tail of the run, not the ramp of a run that starts
  * with few tracks: the first snapshot never starts it; 0xFFFFFFFF drains from
  * the first iteration on), each further
- * iteration fills the vacant slots and then runs one kernel in which every
- * block steps its own tracks in rounds, for up to drain_steps rounds (> 0)
- * of up to 4 steps per track: half of a block's threads own occupied slots
- * and half vacant ones,
- * secondaries go onto the block's stack of 2048 records and threads with a
- * vacant slot take them (the rest go back to the initializer buffer).  It
- * removes the per-iteration launch latency of the last, nearly empty
- * iterations; the physics is the same per-track code.
+ * iteration fills the vacant slots and then runs one launch of the
+ * block-local loops of up to drain_steps (> 0) rounds, until its blocks have
+ * no tracks left (the launch counts as one iteration).  It removes the
+ * per-iteration launch latency of the last, nearly empty iterations; the
+ * physics is the same per-track code.
  *
  * reuse_parent_slot (0/1): a track that ends in a step hands its slot to its
  * first secondary directly, instead of through the initializer buffer and the

@@ -14,6 +14,11 @@ FLAGS = [
     "-munsafe-fp-atomics",
     # no packed FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # no hoisting of loop-invariant machine code: it keeps the constants of
+    # log, exp and sincos in registers across whole kernels, which then spill
+    # or hold fewer waves (k_steps FP64 in a field: 256 registers and 430 bytes
+    # of scratch with it, 220 and none without)
+    "-mllvm", "-disable-machine-licm",
     "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
 ]
 

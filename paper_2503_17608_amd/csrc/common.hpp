@@ -53,6 +53,7 @@ enum : uint8_t {
     A_PROC0 = 4,       // + process index: discrete interaction
     A_ANNIH = A_PROC0 + P_ANNIH,
     A_NUM = A_PROC0 + kNumProc,
+    A_SELECT = 0x40,   // block-local step loops: an interaction whose process is yet to be chosen
     A_NONE = 0xFF      // vacant slot
 };
 
@@ -133,11 +134,8 @@ constexpr int kNumWork = W_DRAIN + 1;
 constexpr int kStepsSlot = kNumWork;
 constexpr int kNumW = 2 * kNumWork;
 static_assert(W_DRAIN < kNumWork, "work counter slots");
-constexpr uint32_t kDrainThreadsMax = 1u << 16;   // drain kernel threads (8 stack records each, per block)
-constexpr int kDrainDepth = 8;                     // private secondary stack depth per drain thread
-constexpr uint32_t kDrainStepsDefault = 4096;      // steps per drain thread and launch
-constexpr int kDrainSubsteps = 1024;               // field substeps per drain trip before a pause
-constexpr int kDrainBurst = 4;                     // steps per track and drain round
+constexpr uint32_t kStackMax = 1u << 19;           // records of all block stacks of the block-local step loops
+constexpr uint32_t kDrainStepsDefault = 4096;      // iterations per drain launch
 
 // Host-visible snapshot copied to pinned memory after each batch
 struct Snapshot {
@@ -193,29 +191,43 @@ template <> __device__ __forceinline__ float unit_from<float>(uint64_t w)
 }
 
 // Uniforms of one track step: uniform j is word j&3 of the Philox block
-// (key, step, j>>2, domain 0) under key (seed, event).
+// (key, step, j>>2, domain 0) under key (seed, event).  The first two blocks
+// are taken at once: a wave's tracks start at different words, so that taken
+// one by one each of them would be computed for a part of the wave at several
+// places; later blocks replace them (one place in the code each).
 template <class R>
 struct StepRng {
     uint64_t k0, k1, key, step;
-    int j;
-    int have;          // block index cached in b0..b3, -1 none
-    uint64_t b0, b1, b2, b3;
-    __device__ StepRng(uint64_t seed, uint64_t event, uint64_t track_key, uint64_t step_, int j0)
-        : k0(seed), k1(event), key(track_key), step(step_), j(j0), have(-1), b0(0), b1(0), b2(0), b3(0) {}
+    uint32_t j;        // next uniform
+    uint32_t first, have;   // the words hold uniforms [first, first + have)
+    uint64_t w0, w1, w2, w3, w4, w5, w6, w7;
+    __device__ __forceinline__ StepRng(uint64_t seed, uint64_t event, uint64_t track_key, uint64_t step_, uint32_t j0)
+        : k0(seed), k1(event), key(track_key), step(step_), j(j0), first(0), have(8)
+    {
+        const U64x4 a = philox4x64_10(key, step, 0, 0, k0, k1), b = philox4x64_10(key, step, 1, 0, k0, k1);
+        w0 = a.w[0]; w1 = a.w[1]; w2 = a.w[2]; w3 = a.w[3];
+        w4 = b.w[0]; w5 = b.w[1]; w6 = b.w[2]; w7 = b.w[3];
+    }
     __device__ __forceinline__ R next()
     {
-        int b = j >> 2;
-        if (b != have) {
-            U64x4 o = philox4x64_10(key, step, (uint64_t)b, 0, k0, k1);
-            b0 = o.w[0]; b1 = o.w[1]; b2 = o.w[2]; b3 = o.w[3];
-            have = b;
+        if (j - first >= have) {
+            const U64x4 o = philox4x64_10(key, step, (uint64_t)(j >> 2), 0, k0, k1);
+            w0 = o.w[0]; w1 = o.w[1]; w2 = o.w[2]; w3 = o.w[3];
+            first = j & ~3u;
+            have = 4;
         }
-        int q = j & 3;
-        uint64_t w = q == 0 ? b0 : (q == 1 ? b1 : (q == 2 ? b2 : b3));
+        const uint32_t q = j - first;
+        const uint64_t a = q & 1u ? w1 : w0, b = q & 1u ? w3 : w2, c = q & 1u ? w5 : w4, e = q & 1u ? w7 : w6;
+        const uint64_t lo = q & 2u ? b : a, hi = q & 2u ? e : c;
         ++j;
-        return unit_from<R>(w);
+        return unit_from<R>(q & 4u ? hi : lo);
     }
 };
+
+// Keeps a product from being fused into a sum that uses it: the value is
+// rounded first, wherever the compiler places the two.
+__device__ __forceinline__ double rounded(double x) { asm volatile("" : "+v"(x)); return x; }
+__device__ __forceinline__ float rounded(float x) { asm volatile("" : "+v"(x)); return x; }
 
 __device__ __forceinline__ uint64_t child_key(uint64_t seed, uint64_t event, uint64_t key, uint64_t step, int ordinal)
 {
@@ -229,6 +241,8 @@ __device__ __forceinline__ double m_exp(double x) { return exp(x); }
 __device__ __forceinline__ float m_exp(float x) { return expf(x); }
 __device__ __forceinline__ double m_sqrt(double x) { return sqrt(x); }
 __device__ __forceinline__ float m_sqrt(float x) { return sqrtf(x); }
+__device__ __forceinline__ double m_fma(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ float m_fma(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double m_floor(double x) { return floor(x); }
 __device__ __forceinline__ float m_floor(float x) { return floorf(x); }
 __device__ __forceinline__ void m_sincos(double x, double* s, double* c) { sincos(x, s, c); }

@@ -6,9 +6,13 @@
 //   -> [sort point 1, by the along-step action of each type]
 //   -> pre-step and along-step (neutral, charged, field; one kernel each)
 //   -> [sort point 2] -> seven interaction kernels, or one fused launch;
-// after each launch group, a completion scan.
-// Below a live-track threshold ems_run replaces the iteration by a fill and
-// one drain launch (block-local step loops).  Loop termination is read from device
+// or, with the partition policy and every launch fused (local_steps), for many
+// iterations at once,
+//   vacancy count / scatter -> initialization -> k_steps,
+// in which every block steps the tracks of its own slots; after each launch
+// group, a completion scan.
+// Below a live-track threshold ems_run drains the last tracks with the same
+// block-local loops.  Loop termination is read from device
 // counters copied asynchronously to a pinned host buffer after every batch of
 // iterations; batches can be captured once into a HIP graph and replayed.  No
 // synchronous memory operation is issued inside the loop (paper,
@@ -51,6 +55,8 @@ ems_status fail(ems_status s, const std::string& msg)
 inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 
 constexpr uint64_t kStagingCap = 1 << 16;   // primaries / row registrations per host-to-device copy
+constexpr uint32_t kStepsPerLaunch = 32;      // rounds of a launch of the block-local step loops in ems_run
+constexpr size_t kStepsLdsMax = 63 << 10;    // dynamic LDS of the block-local step loops (their counters need some more)
 constexpr uint32_t kMaxCounterCopies = 64;   // copies of the per-event counters (a power of two)
 
 // a new event row: {event id, row, registration generation}
@@ -71,7 +77,7 @@ struct Layout {
     uint64_t sec_cnt, sec_blk, sec_rec;    // deterministic appends (staging; 0 when off)
     uint64_t along_list;                   // occupied slots before the fill (masked one-launch along-steps)
     uint32_t part_stride;
-    uint32_t drain_threads;   // capacity of the drain kernel (threads; 8 stack records each)
+    uint32_t stack_records;   // records of all block stacks of the block-local step loops
     uint64_t total;
     uint32_t n_tiles;
 };
@@ -150,8 +156,8 @@ Layout make_layout(const ems_options& o)
     L.part = take(8ull * kNumW * L.part_stride);
     L.rowsum = take(8ull * kNumW);
     L.incr = take(8ull * o.max_materials * 2 * (kNodes - 1));
-    L.drain_threads = (uint32_t)std::min<uint64_t>(kDrainThreadsMax, align_up(n, 256));
-    L.drain_stack = take(sizeof(Initializer) * kDrainDepth * (uint64_t)L.drain_threads);
+    L.stack_records = (uint32_t)std::min<uint64_t>(kStackMax, 8 * align_up(n, 256));
+    L.drain_stack = take(sizeof(Initializer) * (uint64_t)L.stack_records);
     L.regs = take(sizeof(RowReg) * kStagingCap);
     L.ledger_out = take(sizeof(Ledger) * (uint64_t)o.max_events);
     if (o.deterministic) {
@@ -619,15 +625,15 @@ void launch_iteration(ems_ctx* c, bool no_init, bool prof)
     hipStream_t st = c->stream;
     ln.k(R_VAC, true, false, k_vac_count<R>, dim3(nvs), dim3(kVacBlock), 0, st, d);
     ln.k(R_VAC, false, true, k_vac_scatter<R>, dim3(nvs), dim3(kVacBlock), 0, st, d, no_init ? 0 : 1,
-         d.compact_along ? d.along_list : (uint32_t*)nullptr);
+         d.compact_along ? d.along_list : (uint32_t*)nullptr, 1u);
     if (!no_init) {
         if (d.fill_reserve) {
             ln.one(R_INIT, k_init_reserve<R>, dim3(nvb), dim3(kVacBlock), 0, st, d);
         } else if (c->opt.init_partition) {
             ln.k(R_INIT, true, false, k_init_count<R>, dim3(nvb), dim3(kVacBlock), 0, st, d);
-            ln.k(R_INIT, false, true, k_init<R, true>, dim3(nvb), dim3(kVacBlock), 0, st, d);
+            ln.k(R_INIT, false, true, k_init<R, true>, dim3(nvb), dim3(kVacBlock), 0, st, d, 0);
         } else {
-            ln.one(R_INIT, k_init<R, false>, dim3(nvb), dim3(kVacBlock), 0, st, d);
+            ln.one(R_INIT, k_init<R, false>, dim3(nvb), dim3(kVacBlock), 0, st, d, 0);
         }
     }
     const size_t lds = d.stage_tables ? (size_t)d.n_tab * sizeof(R) : 0;
@@ -674,11 +680,27 @@ void launch_iteration_any(ems_ctx* c, bool no_init, bool prof)
     else launch_iteration<double>(c, no_init, prof);
 }
 
-// One drain iteration: vacancies (and the list of occupied slots), fill from
-// the initializer buffer and the pending primaries, then one drain launch in
-// which every block steps its share of the slots in rounds.
+// Slots per block and blocks of the block-local step loops: one block per CU
+// (or fewer, down to one chunk of 64 slots each) up to the most slots a block
+// can hold, more blocks beyond that.
+struct StepsShape {
+    uint32_t per_block, blocks;
+};
+
+StepsShape steps_shape(uint64_t n_slots)
+{
+    const uint64_t chunks = (n_slots + 63) / 64;
+    uint64_t per = (chunks + 255) / 256;
+    if (per > kStepsSlots / 64) per = kStepsSlots / 64;
+    return StepsShape{(uint32_t)(per * 64), (uint32_t)((chunks + per - 1) / per)};
+}
+
+// Up to `n_iter` step iterations in one launch (counted as `n_count`
+// iterations): vacancies, fill from the initializer buffer and the pending
+// primaries, then one launch in which every block steps its share of the
+// slots.  `tail`: the drain of a run's last tracks.
 template <class R>
-void launch_drain(ems_ctx* c, uint32_t threads)
+void launch_steps(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool tail)
 {
     Dev<R> d = make_dev<R>(c);
     Launcher ln{c, c->prof_mask != 0};
@@ -686,19 +708,39 @@ void launch_drain(ems_ctx* c, uint32_t threads)
     const uint32_t nvb = (n + kVacBlock - 1) / kVacBlock;
     const uint32_t nvs = (n + kVacSpan - 1) / kVacSpan;      // vacancy blocks
     hipStream_t st = c->stream;
-    uint32_t* live_list = (uint32_t*)(c->ws + c->L.perm);
+    d.fill_reserve = 0;
     ln.k(R_VAC, true, false, k_vac_count<R>, dim3(nvs), dim3(kVacBlock), 0, st, d);
-    ln.k(R_VAC, false, true, k_vac_scatter<R>, dim3(nvs), dim3(kVacBlock), 0, st, d, 1, live_list);
-    ln.one(R_INIT, k_init<R, false>, dim3(nvb), dim3(kVacBlock), 0, st, d);
-    const size_t lds = d.stage_tables ? (size_t)d.n_tab * sizeof(R) : 0;
-    ln.one(R_DRAIN, k_drain<R>, dim3((threads + 255) / 256), dim3(256), lds, st, d, (const uint32_t*)live_list,
-           (Initializer*)(c->ws + c->L.drain_stack), threads, kDrainDepth, c->drain_steps);
+    ln.k(R_VAC, false, true, k_vac_scatter<R>, dim3(nvs), dim3(kVacBlock), 0, st, d, 1, (uint32_t*)nullptr, n_count);
+    ln.one(R_INIT, k_init<R, false>, dim3(nvb), dim3(kVacBlock), 0, st, d, 1);
+    const StepsShape sh = steps_shape(n);
+    ln.one(R_DRAIN, d.has_field ? k_steps<R, true> : k_steps<R, false>, dim3(sh.blocks), dim3(kStepsThreads),
+           steps_lds(sh.per_block, d.n_tab * sizeof(R)), st, d, (Initializer*)(c->ws + c->L.drain_stack),
+           c->L.stack_records / sh.blocks, sh.per_block, n_iter, sync ? 1 : 0, tail ? 1 : 0);
 }
 
-void launch_drain_any(ems_ctx* c, uint32_t threads)
+void launch_steps_any(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool tail)
 {
-    if (c->opt.precision == EMS_MIXED) launch_drain<float>(c, threads);
-    else launch_drain<double>(c, threads);
+    if (c->opt.precision == EMS_MIXED) launch_steps<float>(c, n_iter, n_count, sync, tail);
+    else launch_steps<double>(c, n_iter, n_count, sync, tail);
+}
+
+// The block-local step loops keep the tables in LDS beside their lists.
+bool steps_fit(const ems_ctx* c)
+{
+    const size_t tables = (size_t)c->n_materials * kTabPerMat * kNodes * (c->opt.precision == EMS_MIXED ? 4 : 8);
+    return steps_lds(steps_shape(c->opt.n_slots).per_block, tables) <= kStepsLdsMax;
+}
+
+// Step iterations run as block-local step loops: slots partitioned by action
+// on one stream with every launch fused.  (The other policies and unfused
+// settings ask for their own kernels, deterministic appends for a fixed
+// order, parent-slot reuse for its own placement, and a profile of the
+// kernels of an iteration for those kernels.)
+bool local_steps(const ems_ctx* c)
+{
+    const uint32_t own = (1u << R_VAC) | (1u << R_INIT) | (1u << R_DRAIN);
+    return c->policy == EMS_SORT_PARTITION && c->fuse_interactions && c->fuse_along && c->n_streams == 1 &&
+           !c->reuse_parent && !c->opt.deterministic && !(c->prof_mask & ~own) && steps_fit(c);
 }
 
 // Record the events whose rows emptied in the iterations launched so far.
@@ -772,8 +814,14 @@ ems_status launch_batch(ems_ctx* c, int iters, bool no_init)
 {
     bool prof = c->prof_mask != 0;
     int gi = c->opt.graph_iterations;
-    if (gi > 0 && !prof && iters == gi) {
-        if (c->stream == nullptr) return fail(EMS_ERR_INVALID_ARG, "graph capture needs a non-null stream");
+    const bool graph = gi > 0 && !prof && iters == gi;
+    if (graph && c->stream == nullptr) return fail(EMS_ERR_INVALID_ARG, "graph capture needs a non-null stream");
+    if (!no_init && local_steps(c)) {
+        // one launch for all of them: nothing to gain from a graph
+        launch_steps_any(c, (uint32_t)iters, (uint32_t)iters, true, false);
+        launch_completions(c);
+        HIP_TRY(hipGetLastError());
+    } else if (graph) {
         if (!c->graph || c->graph_iters != gi || c->graph_no_init != (int)no_init) {
             ems_status s = drop_graph(c);
             if (s != EMS_OK) return s;
@@ -1251,14 +1299,18 @@ ems_status ems_step(ems_ctx* c, uint32_t iterations, ems_counters* out)
     if (s != EMS_OK) return s;
     const uint32_t gi = c->opt.graph_iterations > 0 ? (uint32_t)c->opt.graph_iterations : 0;
     uint32_t done = 0;
+    // (block-local loops: launches of any number of iterations)
+    const uint32_t most = local_steps(c) ? std::max(gi, kStepsPerLaunch) : 1u;
     while (gi > 0 && iterations - done >= gi) {
         s = launch_batch(c, (int)gi, false);
         if (s != EMS_OK) return s;
         done += gi;
     }
-    for (; done < iterations; ++done) {
-        s = launch_batch(c, 1, false);
+    while (done < iterations) {
+        const uint32_t n = std::min(iterations - done, most);
+        s = launch_batch(c, (int)n, false);
         if (s != EMS_OK) return s;
+        done += n;
     }
     if (out) {
         Snapshot sn;
@@ -1275,6 +1327,9 @@ ems_status ems_run(ems_ctx* c, uint64_t max_iterations, ems_counters* out)
     ems_status s = check_ready(c);
     if (s != EMS_OK) return s;
     const int batch = c->opt.graph_iterations > 0 ? c->opt.graph_iterations : 16;
+    const bool local = local_steps(c);
+    if (local && c->opt.graph_iterations > 0 && c->prof_mask == 0 && c->stream == nullptr)
+        return fail(EMS_ERR_INVALID_ARG, "graph capture needs a non-null stream");
     uint64_t launched = 0;
     uint64_t seq = 0;
     // batches in flight: after launching batch g we wait for the snapshot of batch g-1
@@ -1295,16 +1350,19 @@ ems_status ems_run(ems_ctx* c, uint64_t max_iterations, ems_counters* out)
             // snapshot shows the threshold reached again; the largest
             // threshold drains every iteration from the first
             const bool below = c->drain_threshold > 0 && left < c->drain_threshold;
-            draining = c->drain_threshold == UINT32_MAX || (below && (draining || left <= left_before));
+            draining = steps_fit(c) &&
+                       (c->drain_threshold == UINT32_MAX || (below && (draining || left <= left_before)));
             if (draining) {
-                // two threads per track left (half of a block's threads own
-                // vacant slots); before the first snapshot, all of them
-                const uint64_t cap = c->L.drain_threads;
-                const uint64_t want = left >= cap ? cap : align_up(std::max<uint64_t>(2 * left, 256), 256);
-                launch_drain_any(c, (uint32_t)std::min<uint64_t>(want, cap));
+                launch_steps_any(c, c->drain_steps, 1, false, true);
                 launch_completions(c);
                 HIP_TRY(hipGetLastError());
                 launched += 1;
+            } else if (local) {
+                const uint32_t n = (uint32_t)std::min<uint64_t>(kStepsPerLaunch, max_iterations - launched);
+                launch_steps_any(c, n, n, false, false);
+                launch_completions(c);
+                HIP_TRY(hipGetLastError());
+                launched += n;
             } else {
                 s = launch_batch(c, batch, false);
                 if (s != EMS_OK) return s;

@@ -322,10 +322,10 @@ __global__ void __launch_bounds__(kVacBlock) k_vac_count(Dev<R> d)
 // then from the pending primaries.
 //
 // With live_out set, the occupied slots are also listed there in slot order
-// (n_slots - n_vac of them), for the drain kernel and the listed walk of the
-// along-steps.
+// (n_slots - n_vac of them), for the listed walk of the along-steps.
+// `n_iter` step iterations follow.
 template <class R>
-__global__ void __launch_bounds__(kVacBlock) k_vac_scatter(Dev<R> d, int plan_fill, uint32_t* live_out)
+__global__ void __launch_bounds__(kVacBlock) k_vac_scatter(Dev<R> d, int plan_fill, uint32_t* live_out, uint32_t n_iter)
 {
     __shared__ uint32_t red[kVacBlock / 64];
     __shared__ uint32_t wcnt[kVacBlock / 64];
@@ -361,7 +361,7 @@ __global__ void __launch_bounds__(kVacBlock) k_vac_scatter(Dev<R> d, int plan_fi
         uint32_t n_vac = prefix + blk;
         c->n_vac = n_vac;
         c->n_alive = d.n_slots - n_vac;
-        c->iterations += 1;
+        c->iterations += n_iter;
         unsigned long long q = c->queue_size;
         if (q > d.queue_cap) q = d.queue_cap;     // entries past capacity were dropped (overflow flagged)
         unsigned long long pa = c->prim_end - c->prim_next;
@@ -464,13 +464,15 @@ __device__ __forceinline__ const Initializer* taken(const Dev<R>& d, uint32_t i)
 }
 
 // A new track in `slot` from an initializer record.
-template <class R>
+template <class R, bool LOCAL = false>
 __device__ __forceinline__ void init_slot(const Dev<R>& d, uint32_t slot, const Initializer& rec)
 {
     // the path length, search state, step limit and cross section of a
     // step are read only when it resumes from a pause: a new track has none
-    d.type[slot] = rec.type;
-    d.action[slot] = A_IDLE;
+    if (!LOCAL) {
+        d.type[slot] = rec.type;
+        d.action[slot] = A_IDLE;
+    }
     d.flags[slot] = 0;
     d.slab[slot] = rec.slab;
     d.row[slot] = rec.row;
@@ -504,8 +506,10 @@ __global__ void __launch_bounds__(kVacBlock) k_init_count(Dev<R> d)
 // taken initializer goes to the i-th vacancy; with it, charged initializers
 // fill vacancies from the lowest slot upwards and neutral ones from the
 // highest slot downwards (paper, "Partitioning track data").
+// With `spread` the i-th of n initializers goes to the vacancy i / n of the
+// way through them instead, so that every block of k_steps gets its share.
 template <class R, bool PART>
-__global__ void __launch_bounds__(kVacBlock) k_init(Dev<R> d)
+__global__ void __launch_bounds__(kVacBlock) k_init(Dev<R> d, int spread)
 {
     __shared__ uint32_t red[kVacBlock / 64];
     __shared__ uint32_t wcnt[kVacBlock / 64];
@@ -535,7 +539,7 @@ __global__ void __launch_bounds__(kVacBlock) k_init(Dev<R> d)
             d.ctr->n_take_lo = tot;
         }
     } else {
-        if (act) slot = d.vac[i];
+        if (act) slot = d.vac[spread ? (uint32_t)((unsigned long long)i * c->n_vac / n) : i];
     }
     flush_count(d, W_INIT, act ? 1ull : 0ull);
     if (!act) return;
@@ -748,11 +752,13 @@ __device__ __forceinline__ void record_tally(const Dev<R>& d, uint32_t row, int 
 
 // a track finishes: free its slot and add its steps to the event ledger (the
 // global step counter is summed per wavefront by the caller)
-template <class R>
+template <class R, bool LOCAL = false>
 __device__ __forceinline__ void retire(const Dev<R>& d, uint32_t s, uint32_t row, uint32_t steps)
 {
-    d.type[s] = kDead;
-    d.action[s] = A_NONE;
+    if (!LOCAL) {       // block-local step loops keep the slots' types in LDS until they end
+        d.type[s] = kDead;
+        d.action[s] = A_NONE;
+    }
     atomicAdd(&ledger_of(d, row).steps, (unsigned long long)steps);
 }
 
@@ -788,12 +794,14 @@ __device__ __forceinline__ uint32_t reuse_slot(const Dev<R>& d, uint32_t s, SecB
 // its fields once and stores what persists once): draws the interaction
 // length when it is unset, and gives the total cross section, the physics
 // step limit, the step's flags (F_DREW, F_LOSS; a new step starts with no
-// other flag) and the random word of the step's process selection.  The along-step kernels and the drain run it for their tracks
-// before the step; there is no separate pre-step launch.
+// other flag), the random word of the step's process selection, and for the
+// end of the step the energy's place in the tables and, for a lepton, its
+// range.  The along-step kernels and the block-local loops run it for their
+// tracks before the step; there is no separate pre-step launch.
 template <class R>
 __device__ __forceinline__ void pre_step(const Dev<R>& d, const Tables<R>& tb, int mat, int typ, R T, R& nl,
                                          uint64_t event, uint64_t key, uint32_t step, R& sig, double& s_phys,
-                                         uint8_t& nf, uint64_t& w_sel)
+                                         uint8_t& nf, uint64_t& w_sel, Loc<R>& l, R& Rg)
 {
     // Block 0 of the step's uniforms, computed once: word 0 is the
     // interaction-length uniform when one is drawn, and the next unused word
@@ -808,12 +816,12 @@ __device__ __forceinline__ void pre_step(const Dev<R>& d, const Tables<R>& tb, i
         nf |= F_DREW;
         w_sel = b0.w[1];
     }
-    Loc<R> l = locate(tb, T);
-    sig = total_xs(tb, mat, typ, T, l, R(d.ecut));
+    l = locate(tb, T);
+    sig = total_xs(proc_xs(tb, mat, typ, T, l, R(d.ecut)), typ);
     R s_int = sig > R(0) ? nl / sig : R(INFINITY);
     R sp = s_int;
     if (typ != kGamma) {
-        R Rg = interp(range_tab(tb, mat, typ), l);
+        Rg = interp(range_tab(tb, mat, typ), l);
         R s_loss = Rg <= R(kRFinal) ? Rg : m_max(R(kRFinal), R(kRhoRange) * Rg);
         if (s_loss < s_int) {
             sp = s_loss;
@@ -837,6 +845,16 @@ __device__ __forceinline__ double face_plane(const double* zp, int slab, double 
     }
 }
 __device__ __forceinline__ int face_axis(int face) { return face <= F_ZHI ? 2 : (face <= F_XHI ? 0 : 1); }
+
+// Put a point onto the plane v of a face.  (Selects: an index chosen at run
+// time would keep the point in scratch memory.)
+__device__ __forceinline__ void snap(double r[3], int face, double v)
+{
+    const int ax = face_axis(face);
+    r[0] = ax == 0 ? v : r[0];
+    r[1] = ax == 1 ? v : r[1];
+    r[2] = ax == 2 ? v : r[2];
+}
 
 // straight-line distance to leave the slab box (z face wins ties, then x, y)
 __device__ __forceinline__ double straight_distance(const double r[3], const double u[3], double zlo, double zhi,
@@ -904,29 +922,62 @@ __device__ __forceinline__ bool stop_defers(const Dev<R>& d, int typ, R& T, Step
     return false;
 }
 
+// The step guard (more than kMaxSteps steps): the track stops after its
+// (counted) step; a positron annihilates at rest with the counted step's
+// index.
+template <class R>
+__device__ __forceinline__ void guard_stop(const Dev<R>& d, uint32_t row, int typ, R& T, uint8_t& fl, StepTally& tl,
+                                           bool& alive, uint8_t& next_action)
+{
+    atomicAdd(&ledger_of(d, row).n_guard, 1ull);
+    if (typ == kGamma) {
+        tl.edep += (double)T;
+        T = R(0);
+        alive = false;
+        next_action = A_NONE;
+    } else if (stop_defers(d, typ, T, tl)) {
+        next_action = A_ANNIH;
+        fl = (uint8_t)((fl & (uint8_t)~F_PAUSED) | F_COUNTED);
+    } else {
+        alive = false;
+        next_action = A_NONE;
+    }
+}
+
+// The discrete process of an interaction, from the cross sections of the
+// particle's processes, their sum sig1 > 0 and the uniform U1.
+template <class R>
+__device__ __forceinline__ uint8_t select_process(const ProcXs<R>& xs, int typ, R sig1, R U1)
+{
+    const R target = U1 * sig1;
+    const R one = xs.x[0], two = xs.x[0] + xs.x[1];
+    const int n = target < one ? 0 : (typ == kGamma && !(target < two) ? 2 : 1);
+    return (uint8_t)(A_PROC0 + proc_of(typ, n));
+}
+
 // Common end of an along-step (S6-S8) for a step of length step_len: energy
 // loss, the stop, boundary crossing or escape, the choice of the discrete
 // process, the step guard.  Clears `alive` when the track ends and sets the
 // next action; a positron that stops stays alive with A_ANNIH (annihilation
 // at rest, done by the interaction launch), so no along-step creates tracks.
-template <class R, bool CHARGED>
+// With LOCAL (block-local step loops) a step that ends in an interaction
+// leaves the choice of its process to a later pass (A_SELECT).
+template <class R, bool CHARGED, bool LOCAL>
 __device__ __forceinline__ void finish_along(const Dev<R>& d, const Tables<R>& tb, int typ, R& T, R sig, double step_len,
                                              int face, uint8_t& fl, int mat, uint16_t& slab, StepTally& tl,
                                              bool& alive, uint8_t& next_action, R& nl, uint32_t& step, uint64_t key,
-                                             uint64_t event, uint32_t row, bool have_sel, uint64_t w_sel)
+                                             uint64_t event, uint32_t row, bool have_sel, uint64_t w_sel,
+                                             const Loc<R>& l, R Rg)
 {
     // step, key and row come in registers (loaded with the rest of the
     // track up front); step leaves as the track's step count after this step
     const uint32_t k = step;
     if (CHARGED) {
-        const R* Rt = range_tab(tb, mat, typ);
-        Loc<R> l = locate(tb, T);
-        R Rg = interp(Rt, l);
         bool stop = false;
         if (face == F_NONE && (fl & F_LOSS) && Rg <= R(kRFinal)) {
             stop = true;
         } else {
-            R Tn = inverse_range(tb, Rt, (R)((double)Rg - step_len), l.i + 1);
+            R Tn = inverse_range(tb, range_tab(tb, mat, typ), (R)((double)Rg - step_len), l.i);
             if (Tn < R(d.ecut)) stop = true;
             else {
                 tl.edep += (double)T - (double)Tn;
@@ -962,6 +1013,10 @@ __device__ __forceinline__ void finish_along(const Dev<R>& d, const Tables<R>& t
     } else if (fl & F_LOSS) {
         next_action = A_IDLE;
         step = k + 1;
+    } else if (LOCAL) {
+        nl = R(-1);
+        next_action = A_SELECT;
+        return;
     } else {
         // the process-selection uniform: kept from the pre-step's block, or
         // (a step resumed after a pause, which ran no pre-step) drawn here
@@ -972,42 +1027,17 @@ __device__ __forceinline__ void finish_along(const Dev<R>& d, const Tables<R>& t
             StepRng<R> rng(d.seed, event, key, k, (fl & F_DREW) ? 1 : 0);
             U1 = rng.next();
         }
-        R sig1;
-        Loc<R> l1;
-        l1 = locate(tb, T);
-        if (CHARGED) sig1 = total_xs(tb, mat, typ, T, l1, R(d.ecut));
-        else sig1 = sig;
+        const ProcXs<R> xs = proc_xs(tb, mat, typ, T, CHARGED ? locate(tb, T) : l, R(d.ecut));
+        const R sig1 = CHARGED ? total_xs(xs, typ) : sig;
         nl = R(-1);
         if (sig1 > R(0)) {
-            R target = U1 * sig1, cum = R(0);
-            int proc = proc_of(typ, n_proc(typ) - 1);
-            for (int k = 0; k < n_proc(typ); ++k) {
-                cum += proc_xs(tb, mat, proc_of(typ, k), T, l1, R(d.ecut));
-                if (target < cum) { proc = proc_of(typ, k); break; }
-            }
-            next_action = (uint8_t)(A_PROC0 + proc);
+            next_action = select_process(xs, typ, sig1, U1);
         } else {
             next_action = A_IDLE;
             step = k + 1;
         }
     }
-    if (alive && step > kMaxSteps && next_action == A_IDLE) {
-        // step guard: the track stops after this (counted) step; a positron
-        // annihilates at rest with the counted step's index
-        atomicAdd(&ledger_of(d, row).n_guard, 1ull);
-        if (typ == kGamma) {
-            tl.edep += (double)T;
-            T = R(0);
-            alive = false;
-            next_action = A_NONE;
-        } else if (stop_defers(d, typ, T, tl)) {
-            next_action = A_ANNIH;
-            fl = (uint8_t)((fl & (uint8_t)~F_PAUSED) | F_COUNTED);
-        } else {
-            alive = false;
-            next_action = A_NONE;
-        }
-    }
+    if (alive && step > kMaxSteps && next_action == A_IDLE) guard_stop(d, row, typ, T, fl, tl, alive, next_action);
 }
 
 // Along-step of one straight-line track (photon, or charged without field),
@@ -1015,11 +1045,10 @@ __device__ __forceinline__ void finish_along(const Dev<R>& d, const Tables<R>& t
 // registers and what persists goes back to the slot once; the step's deposit
 // goes to its tally row.  `row` is the track's row, `next` the next action,
 // `retired` the steps of a track that finished (0 while it lives).
-template <class R, bool CHARGED>
-__device__ __forceinline__ void along_straight_track(const Dev<R>& d, const Tables<R>& tb, uint32_t s, uint32_t& row,
-                                                     uint8_t& next, uint32_t& retired)
+template <class R, bool CHARGED, bool LOCAL>
+__device__ __forceinline__ void along_straight_track(const Dev<R>& d, const Tables<R>& tb, uint32_t s, int typ,
+                                                     uint32_t& row, uint8_t& next, uint32_t& retired)
 {
-    const int typ = d.type[s];
     row = d.row[s];
     uint16_t slab = d.slab[s];
     const uint16_t slab0 = slab;
@@ -1036,7 +1065,9 @@ __device__ __forceinline__ void along_straight_track(const Dev<R>& d, const Tabl
     double s_phys;
     uint8_t fl;
     uint64_t w_sel;
-    pre_step(d, tb, mat, typ, T, nl, event, key, step, sig, s_phys, fl, w_sel);
+    Loc<R> l;
+    R Rg = R(0);
+    pre_step(d, tb, mat, typ, T, nl, event, key, step, sig, s_phys, fl, w_sel, l, Rg);
     double ud[3] = {(double)u[0], (double)u[1], (double)u[2]};
     int face;
     double s_geo = straight_distance(r, ud, d.zp[slab], d.zp[slab + 1], d.W, &face);
@@ -1046,14 +1077,14 @@ __device__ __forceinline__ void along_straight_track(const Dev<R>& d, const Tabl
     r[0] = r[0] + st * ud[0];
     r[1] = r[1] + st * ud[1];
     r[2] = r[2] + st * ud[2];
-    if (face != F_NONE) r[face_axis(face)] = face_plane(d.zp, slab, d.W, face);
+    if (face != F_NONE) snap(r, face, face_plane(d.zp, slab, d.W, face));
     StepTally tl = {0.0, 0, 0, 0};
     bool alive = true;
     uint8_t na = A_IDLE;
     const uint32_t k0 = step;
     const double T_pre = (double)T;
-    finish_along<R, CHARGED>(d, tb, typ, T, sig, st, face, fl, mat, slab, tl, alive, na, nl, step, key, event, row,
-                             true, w_sel);
+    finish_along<R, CHARGED, LOCAL>(d, tb, typ, T, sig, st, face, fl, mat, slab, tl, alive, na, nl, step, key, event,
+                                    row, true, w_sel, l, Rg);
     record_tally(d, row, slab0, tl);
     if (alive) {
         // the whole record is written (whole 32-byte sectors, no partial
@@ -1078,11 +1109,11 @@ __device__ __forceinline__ void along_straight_track(const Dev<R>& d, const Tabl
         if (slab != slab0) d.slab[s] = slab;
         if (step != k0) d.step[s] = step;
         d.flags[s] = fl;
-        d.action[s] = na;
+        if (!LOCAL) d.action[s] = na;
         next = na;
     } else {
         retired = step;
-        retire(d, s, row, retired);
+        retire<R, LOCAL>(d, s, row, retired);
     }
 }
 
@@ -1101,7 +1132,7 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_along_straight(Dev<R> d)
     uint32_t retired = 0;
     if (act) {
         ++pre_acc;
-        along_straight_track<R, CHARGED>(d, tb, s, row, next, retired);
+        along_straight_track<R, CHARGED, false>(d, tb, s, d.type[s], row, next, retired);
     }
     leave_event(d, retired != 0, row);
     ret_acc += retired;
@@ -1168,6 +1199,94 @@ __device__ __forceinline__ void normalize_d(double v[3])
     v[0] /= n; v[1] /= n; v[2] /= n;
 }
 
+// State of a field step between two RK4 evaluations, and the crossed face
+// once it has ended.
+struct FieldStep {
+    double r[3], u[3];
+    double s_done, h_try;
+    int n_search, face;
+};
+
+// One RK4 evaluation of a field step (S5): the substep is accepted, ends the
+// step on a face, or is to be tried again shorter.  Returns true when the
+// step has ended.
+template <class R>
+__device__ __forceinline__ bool field_substep(const Dev<R>& d, int slab, double zlo, double zhi, double kf,
+                                              double h_chord, double s_phys, FieldStep& f)
+{
+    const double rem = s_phys - f.s_done;
+    const double h = f.h_try > 0.0 ? f.h_try : fmin(rem, h_chord);
+    const bool last = (f.h_try == 0.0 && h == rem);
+    double r1[3], u1[3];
+    rk4(f.r, f.u, h, kf, d.B, r1, u1);
+    // first face crossed by the chord r -> r1 (at most one face of each axis)
+    int fc = F_NONE;
+    double fm = INFINITY;
+    for (int k = 0; k < 3; ++k) {
+        const int lo = k == 0 ? F_ZLO : (k == 1 ? F_XLO : F_YLO), ax = face_axis(lo);
+        const double pl = k == 0 ? zlo : -d.W, ph = k == 0 ? zhi : d.W;
+        const bool below = r1[ax] < pl;
+        if (!below && !(r1[ax] > ph)) continue;
+        double fr = ((below ? pl : ph) - f.r[ax]) / (r1[ax] - f.r[ax]);
+        fr = fr < 0.0 ? 0.0 : (fr > 1.0 ? 1.0 : fr);
+        if (fr < fm) { fm = fr; fc = below ? lo : lo + 1; }
+    }
+    if (fc == F_NONE) {
+        int nf = F_NONE;
+        if (f.h_try > 0.0) {
+            double bd = kDInt;
+            for (int fa = F_ZLO; fa <= F_YHI; ++fa) {
+                double pl = fa == F_ZLO ? zlo : (fa == F_ZHI ? zhi : face_plane(d.zp, slab, d.W, fa));
+                double dd = fabs(r1[face_axis(fa)] - pl);
+                if (dd <= bd && (nf == F_NONE || dd < bd)) { bd = dd; nf = fa; }
+            }
+        }
+        f.r[0] = r1[0]; f.r[1] = r1[1]; f.r[2] = r1[2];
+        normalize_d(u1);
+        store_dir<R>(u1);
+        f.u[0] = u1[0]; f.u[1] = u1[1]; f.u[2] = u1[2];
+        if (nf != F_NONE) {
+            snap(f.r, nf, face_plane(d.zp, slab, d.W, nf));
+            f.s_done += h;
+            f.face = nf;
+            return true;
+        }
+        if (last) {
+            f.s_done = s_phys;
+            return true;
+        }
+        f.s_done += h;
+        f.h_try = 0.0;
+        f.n_search = 0;
+        return false;
+    }
+    if (fm == 0.0 && points_out(f.u, fc)) {
+        snap(f.r, fc, face_plane(d.zp, slab, d.W, fc));
+        f.face = fc;
+        return true;
+    }
+    double ch[3] = {r1[0] - f.r[0], r1[1] - f.r[1], r1[2] - f.r[2]};
+    double clen = sqrt(ch[0] * ch[0] + ch[1] * ch[1] + ch[2] * ch[2]);
+    if ((1.0 - fm) * clen <= kDInt || f.n_search >= kMaxSearch) {
+        for (int c = 0; c < 3; ++c) f.r[c] = f.r[c] + fm * ch[c];
+        snap(f.r, fc, face_plane(d.zp, slab, d.W, fc));
+        normalize_d(u1);
+        store_dir<R>(u1);
+        f.u[0] = u1[0]; f.u[1] = u1[1]; f.u[2] = u1[2];
+        f.s_done += fm * h;
+        f.face = fc;
+        return true;
+    }
+    f.h_try = fm > 0.0 ? fm * h : 0.5 * h;
+    f.n_search += 1;
+    return false;
+}
+
+// Which part of a field step a call makes: all of it; its pre-step and first
+// RK4 evaluation (a step that needs more is left paused); or the rest of a
+// paused one.
+enum : int { STEP_ALL = 0, STEP_FIRST, STEP_REST };
+
 // Along-step of one charged track in the uniform field, its pre-step first
 // unless the step resumes from a pause, with at most `max_sub` RK4
 // evaluations (0: no cap) before the step pauses.  The track's fields are
@@ -1190,9 +1309,9 @@ struct FieldIn {
 };
 
 template <class R>
-__device__ __forceinline__ void load_field_in(const Dev<R>& d, uint32_t s, FieldIn<R>& f)
+__device__ __forceinline__ void load_field_in(const Dev<R>& d, uint32_t s, uint8_t typ, FieldIn<R>& f)
 {
-    f.typ = d.type[s];
+    f.typ = typ;
     f.fl = d.flags[s];
     f.slab = d.slab[s];
     f.row = d.row[s];
@@ -1205,7 +1324,7 @@ __device__ __forceinline__ void load_field_in(const Dev<R>& d, uint32_t s, Field
     f.r[0] = tr.r[0]; f.r[1] = tr.r[1]; f.r[2] = tr.r[2];
 }
 
-template <class R>
+template <class R, bool LOCAL = false, int PART = STEP_ALL>
 __device__ __forceinline__ void along_field_track(const Dev<R>& d, const Tables<R>& tb, uint32_t s,
                                                   const FieldIn<R>& in, int max_sub, uint32_t& row, uint8_t& next,
                                                   uint32_t& retired, uint32_t& att, uint32_t& paused_n,
@@ -1217,27 +1336,34 @@ __device__ __forceinline__ void along_field_track(const Dev<R>& d, const Tables<
     const uint16_t slab0 = slab;
     const int mat = d.smat[slab];
     R T = in.T;
-    double u[3] = {(double)in.u[0], (double)in.u[1], (double)in.u[2]};
-    double r[3] = {in.r[0], in.r[1], in.r[2]};
+    FieldStep f;
+    f.r[0] = in.r[0]; f.r[1] = in.r[1]; f.r[2] = in.r[2];
+    f.u[0] = (double)in.u[0]; f.u[1] = (double)in.u[1]; f.u[2] = (double)in.u[2];
+    f.s_done = 0.0;
+    f.h_try = 0.0;
+    f.n_search = 0;
+    f.face = F_NONE;
     uint8_t fl = in.fl;
     R nl = in.nl;
     uint32_t step = in.step;
     const uint64_t key = in.key;
     const uint64_t event = d.row_event[row];
-    const bool resumed = (fl & F_PAUSED) != 0;
-    double s_phys, s_done = 0.0, h_try = 0.0;
-    int n_search = 0;
-    R sig;
+    const bool resumed = PART == STEP_ALL ? (fl & F_PAUSED) != 0 : PART == STEP_REST;
+    double s_phys;
+    R sig, Rg = R(0);
+    Loc<R> l;
     uint64_t w_sel = 0;
     if (resumed) {
         s_phys = d.sphys[s];
-        s_done = d.sdone[s];
-        h_try = d.htry[s];
-        n_search = d.nsearch[s];
+        f.s_done = d.sdone[s];
+        f.h_try = d.htry[s];
+        f.n_search = d.nsearch[s];
         sig = d.xs[s];
+        l = locate(tb, T);
+        Rg = interp(range_tab(tb, mat, typ), l);
         pre_n = 0;
     } else {
-        pre_step(d, tb, mat, typ, T, nl, event, key, step, sig, s_phys, fl, w_sel);
+        pre_step(d, tb, mat, typ, T, nl, event, key, step, sig, s_phys, fl, w_sel, l, Rg);
         pre_n = 1;
     }
     double Td = (double)T;
@@ -1247,89 +1373,28 @@ __device__ __forceinline__ void along_field_track(const Dev<R>& d, const Tables<
     double Bm = sqrt(d.B[0] * d.B[0] + d.B[1] * d.B[1] + d.B[2] * d.B[2]);
     double h_chord = sqrt(8.0 * kDChord / (kCk * Bm / p));
     double zlo = d.zp[slab], zhi = d.zp[slab + 1];
-    int face = F_NONE;
     bool paused = false;
     for (;;) {
-        if (max_sub > 0 && att >= (uint32_t)max_sub) { paused = true; break; }
-        double rem = s_phys - s_done;
-        double h = h_try > 0.0 ? h_try : fmin(rem, h_chord);
-        bool last = (h_try == 0.0 && h == rem);
-        double r1[3], u1[3];
-        rk4(r, u, h, kf, d.B, r1, u1);
+        if (PART == STEP_FIRST ? att >= 1u : (max_sub > 0 && att >= (uint32_t)max_sub)) { paused = true; break; }
         ++att;
-        // first face crossed by the chord r -> r1
-        int fc = F_NONE;
-        double f = INFINITY;
-        for (int fa = F_ZLO; fa <= F_YHI; ++fa) {
-            int ax = face_axis(fa);
-            double pl = fa == F_ZLO ? zlo : (fa == F_ZHI ? zhi : face_plane(d.zp, slab, d.W, fa));
-            if (!beyond(fa, r1[ax], pl)) continue;
-            double fr = (pl - r[ax]) / (r1[ax] - r[ax]);
-            fr = fr < 0.0 ? 0.0 : (fr > 1.0 ? 1.0 : fr);
-            if (fr < f) { f = fr; fc = fa; }
-        }
-        if (fc == F_NONE) {
-            int nf = F_NONE;
-            if (h_try > 0.0) {
-                double bd = kDInt;
-                for (int fa = F_ZLO; fa <= F_YHI; ++fa) {
-                    double pl = fa == F_ZLO ? zlo : (fa == F_ZHI ? zhi : face_plane(d.zp, slab, d.W, fa));
-                    double dd = fabs(r1[face_axis(fa)] - pl);
-                    if (dd <= bd && (nf == F_NONE || dd < bd)) { bd = dd; nf = fa; }
-                }
-            }
-            r[0] = r1[0]; r[1] = r1[1]; r[2] = r1[2];
-            normalize_d(u1);
-            store_dir<R>(u1);
-            u[0] = u1[0]; u[1] = u1[1]; u[2] = u1[2];
-            if (nf != F_NONE) {
-                r[face_axis(nf)] = face_plane(d.zp, slab, d.W, nf);
-                s_done += h;
-                face = nf;
-                break;
-            }
-            if (last) { s_done = s_phys; break; }
-            s_done += h;
-            h_try = 0.0;
-            n_search = 0;
-            continue;
-        }
-        if (f == 0.0 && points_out(u, fc)) {
-            r[face_axis(fc)] = face_plane(d.zp, slab, d.W, fc);
-            face = fc;
-            break;
-        }
-        double ch[3] = {r1[0] - r[0], r1[1] - r[1], r1[2] - r[2]};
-        double clen = sqrt(ch[0] * ch[0] + ch[1] * ch[1] + ch[2] * ch[2]);
-        if ((1.0 - f) * clen <= kDInt || n_search >= kMaxSearch) {
-            for (int c = 0; c < 3; ++c) r[c] = r[c] + f * ch[c];
-            r[face_axis(fc)] = face_plane(d.zp, slab, d.W, fc);
-            normalize_d(u1);
-            store_dir<R>(u1);
-            u[0] = u1[0]; u[1] = u1[1]; u[2] = u1[2];
-            s_done += f * h;
-            face = fc;
-            break;
-        }
-        h_try = f > 0.0 ? f * h : 0.5 * h;
-        n_search += 1;
+        if (field_substep(d, slab, zlo, zhi, kf, h_chord, s_phys, f)) break;
     }
     paused_n = paused ? 1u : 0u;
     if (paused) {
         // the kinetic energy changes only at the end of the step
         TrackRec<R> out;
-        out.r[0] = r[0];
-        out.r[1] = r[1];
-        out.r[2] = r[2];
+        out.r[0] = f.r[0];
+        out.r[1] = f.r[1];
+        out.r[2] = f.r[2];
         out.key = key;
-        out.u[0] = (R)u[0];
-        out.u[1] = (R)u[1];
-        out.u[2] = (R)u[2];
+        out.u[0] = (R)f.u[0];
+        out.u[1] = (R)f.u[1];
+        out.u[2] = (R)f.u[2];
         out.T = in.T;
         store_track(d, s, out);
-        d.sdone[s] = s_done;
-        d.htry[s] = h_try;
-        d.nsearch[s] = (uint8_t)n_search;
+        d.sdone[s] = f.s_done;
+        d.htry[s] = f.h_try;
+        d.nsearch[s] = (uint8_t)f.n_search;
         d.flags[s] = fl | F_PAUSED;
         if (!resumed) {
             // the step limit, cross section and interaction length of the
@@ -1337,7 +1402,7 @@ __device__ __forceinline__ void along_field_track(const Dev<R>& d, const Tables<
             d.sphys[s] = s_phys;
             d.xs[s] = sig;
             d.nl[s] = nl;
-            d.action[s] = A_FIELD;
+            if (!LOCAL) d.action[s] = A_FIELD;
         }
         return;
     }
@@ -1346,30 +1411,30 @@ __device__ __forceinline__ void along_field_track(const Dev<R>& d, const Tables<
     bool alive = true;
     uint8_t na = A_IDLE;
     const uint32_t k0 = step;
-    finish_along<R, true>(d, tb, typ, T, sig, s_done, face, fl, mat, slab, tl, alive, na, nl, step, key, event, row,
-                          !resumed, w_sel);
+    finish_along<R, true, LOCAL>(d, tb, typ, T, sig, f.s_done, f.face, fl, mat, slab, tl, alive, na, nl, step, key,
+                                 event, row, !resumed, w_sel, l, Rg);
     record_tally(d, row, slab0, tl);
     if (alive) {
-        if (d.msc && na != A_ANNIH) msc_deflect(d.seed, event, key, k0, Td, s_done, d.x0[mat], u);
+        if (d.msc && na != A_ANNIH) msc_deflect(d.seed, event, key, k0, Td, f.s_done, d.x0[mat], f.u);
         TrackRec<R> tr;
-        tr.r[0] = r[0];
-        tr.r[1] = r[1];
-        tr.r[2] = r[2];
+        tr.r[0] = f.r[0];
+        tr.r[1] = f.r[1];
+        tr.r[2] = f.r[2];
         tr.key = key;
-        tr.u[0] = (R)u[0];
-        tr.u[1] = (R)u[1];
-        tr.u[2] = (R)u[2];
+        tr.u[0] = (R)f.u[0];
+        tr.u[1] = (R)f.u[1];
+        tr.u[2] = (R)f.u[2];
         tr.T = T;
         store_track(d, s, tr);
         d.nl[s] = nl;
         if (slab != slab0) d.slab[s] = slab;
         if (step != k0) d.step[s] = step;
         d.flags[s] = fl;
-        d.action[s] = na;
+        if (!LOCAL) d.action[s] = na;
         next = na;
     } else {
         retired = step;
-        retire(d, s, row, retired);
+        retire<R, LOCAL>(d, s, row, retired);
     }
 }
 
@@ -1379,7 +1444,7 @@ __device__ __forceinline__ void along_field_track(const Dev<R>& d, const Tables<
                                                   uint32_t& paused_n, uint32_t& pre_n)
 {
     FieldIn<R> in;
-    load_field_in(d, s, in);
+    load_field_in(d, s, d.type[s], in);
     along_field_track<R>(d, tb, s, in, max_sub, row, next, retired, att, paused_n, pre_n);
 }
 
@@ -1424,13 +1489,13 @@ __device__ __forceinline__ void field_tracks_sorted(const Dev<R>& d, const Table
     uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     uint32_t s = i < n ? d.perm[off + i] : 0u;
     FieldIn<R> cur;
-    if (i < n) load_field_in(d, s, cur);
+    if (i < n) load_field_in(d, s, d.type[s], cur);
     uint32_t s_next = i + stride < n ? d.perm[off + i + stride] : 0u;
     for (uint32_t base = blockIdx.x * blockDim.x; base < n; base += stride) {
         const bool act = i < n;
         const uint32_t i1 = i + stride, i2 = i + 2 * stride;
         FieldIn<R> nxt;
-        if (i1 < n) load_field_in(d, s_next, nxt);
+        if (i1 < n) load_field_in(d, s_next, d.type[s_next], nxt);
         const uint32_t s_after = i2 < n ? d.perm[off + i2] : 0u;
         field_step_loaded(d, tb, s, cur, act, acc);
         i = i1;
@@ -1453,7 +1518,7 @@ __device__ __forceinline__ void along_any_track(const Dev<R>& d, const Tables<R>
         ++acc.field;
         acc.ret_field += retired;
     } else if (a == A_NEUTRAL) {
-        along_straight_track<R, false>(d, tb, s, row, next, retired);
+        along_straight_track<R, false, false>(d, tb, s, kGamma, row, next, retired);
         pre_n = 1;
         ++acc.photon;
         acc.ret_photon += retired;
@@ -1548,11 +1613,11 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_along_both(Dev<R> d)
         uint8_t a = p < np_all ? along_action(d, s) : A_NONE;
         uint8_t a1 = p + stride < np_all ? along_action(d, s1) : A_NONE;
         FieldIn<R> cur;
-        if (a == A_FIELD) load_field_in(d, s, cur);
+        if (a == A_FIELD) load_field_in(d, s, d.type[s], cur);
         for (uint32_t base = blockIdx.x * blockDim.x; base < np_all; base += stride) {
             const uint32_t p2 = p + 2 * stride;
             FieldIn<R> nxt;
-            if (a1 == A_FIELD) load_field_in(d, s1, nxt);
+            if (a1 == A_FIELD) load_field_in(d, s1, d.type[s1], nxt);
             const uint32_t s2 = p2 < np_all ? slot_at(p2) : 0u;
             const uint8_t a2 = p2 < np_all ? along_action(d, s2) : A_NONE;
             if (a == A_FIELD) field_step_loaded(d, tb, s, cur, true, acc);
@@ -1574,11 +1639,11 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_along_both(Dev<R> d)
     flush_count_shared(d, W_PRE, acc.pre);
 }
 
-// Discrete interaction PROC of one track at the end of its along-step.
+// Discrete interaction `proc` of one track at the end of its along-step.
 // Outputs as for the along-step (the secondaries start at the track's point).
-template <class R, int PROC>
-__device__ __forceinline__ void interact_track(const Dev<R>& d, uint32_t s, SecBuf<R>& sb, double r[3], uint32_t& row,
-                                               uint16_t& slab, uint32_t& retired)
+template <class R, bool LOCAL = false>
+__device__ __forceinline__ void interact_track(const Dev<R>& d, int proc, uint32_t s, int typ, SecBuf<R>& sb,
+                                               double r[3], uint32_t& row, uint16_t& slab, uint32_t& retired)
 {
     row = d.row[s];
     slab = d.slab[s];
@@ -1589,34 +1654,19 @@ __device__ __forceinline__ void interact_track(const Dev<R>& d, uint32_t s, SecB
     p.u[0] = tr.u[0]; p.u[1] = tr.u[1]; p.u[2] = tr.u[2];
     p.key = tr.key;
     p.step = d.step[s];
-    p.type = d.type[s];
+    p.type = typ;
     p.alive = true;
     uint8_t fl = d.flags[s];
     PhysParams pp = {d.seed, d.row_event[row], d.ecut};
-    StepRng<R> rng(d.seed, pp.event, p.key, p.step, (fl & F_DREW) ? 2 : 1);
     StepTally tl = {0.0, 0, 0, 0};
-    switch (PROC) {
-    case P_COMPTON: sample_compton<R>(pp, p, rng, sb, tl); break;
-    case P_PHOTO:   sample_photo<R>(pp, p, sb, tl); break;
-    case P_PAIR:    sample_pair<R>(pp, p, rng, sb, tl); break;
-    case P_MOLLER:  sample_moller<R>(pp, p, rng, sb, tl); break;
-    case P_BHABHA:  sample_bhabha<R>(pp, p, rng, sb, tl); break;
-    case P_BREMS:   sample_brems<R>(pp, p, rng, sb, tl); break;
-    default:
-        // at rest (the kinetic energy was deposited by the along-step)
-        annihilate<R>(pp, p.key, p.step, sb, tl);
-        p.T = R(0);
-        p.alive = false;
-        break;
-    }
+    interact<R>(pp, proc, p, (fl & F_DREW) ? 2u : 1u, sb, tl);
     // a step-guard stop was counted by the along-step already
-    uint32_t steps = (PROC == P_ANNIH && (fl & F_COUNTED)) ? p.step : p.step + 1;
+    uint32_t steps = (proc == P_ANNIH && (fl & F_COUNTED)) ? p.step : p.step + 1;
     d.step[s] = steps;
     if (p.alive && steps > kMaxSteps) {
         atomicAdd(&ledger_of(d, row).n_guard, 1ull);
         p.step = steps;
-        if (p.type != kGamma) stop_lepton<R>(pp, p, sb, tl);
-        else { tl.edep += (double)p.T; p.alive = false; }
+        if (stop_lepton<R>(p, tl)) annihilate<R>(pp, p.key, p.step, sb, tl);
     }
     record_tally(d, row, slab, tl);
     if (p.alive) {
@@ -1631,10 +1681,10 @@ __device__ __forceinline__ void interact_track(const Dev<R>& d, uint32_t s, SecB
         out.T = p.T;
         store_track(d, s, out);
         d.nl[s] = R(-1);
-        d.action[s] = A_IDLE;
+        if (!LOCAL) d.action[s] = A_IDLE;
     } else {
         retired = steps;
-        retire(d, s, row, steps);
+        retire<R, LOCAL>(d, s, row, steps);
     }
 }
 
@@ -1651,7 +1701,7 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact(Dev<R> d)
     uint32_t row = 0;
     uint16_t slab = 0;
     uint32_t retired = 0;
-    if (act) interact_track<R, PROC>(d, s, sb, r, row, slab, retired);
+    if (act) interact_track<R>(d, PROC, s, d.type[s], sb, r, row, slab, retired);
     if (retired) reuse_acc += reuse_slot(d, s, sb, row, slab, r);
     append_secondaries<R, DET>(d, sb, row, slab, r, retired != 0, _off + _i);
     ret_acc += retired;
@@ -1725,15 +1775,15 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact_all(Dev<R> d)
         uint16_t slab = 0;
         uint32_t retired = 0;
         if (act) {
-            switch (a - A_PROC0) {
-            case P_COMPTON: interact_track<R, P_COMPTON>(d, s, sb, r, row, slab, retired); ++w0; break;
-            case P_PHOTO:   interact_track<R, P_PHOTO>(d, s, sb, r, row, slab, retired); ++w1; break;
-            case P_PAIR:    interact_track<R, P_PAIR>(d, s, sb, r, row, slab, retired); ++w2; break;
-            case P_MOLLER:  interact_track<R, P_MOLLER>(d, s, sb, r, row, slab, retired); ++w3; break;
-            case P_BHABHA:  interact_track<R, P_BHABHA>(d, s, sb, r, row, slab, retired); ++w4; break;
-            case P_BREMS:   interact_track<R, P_BREMS>(d, s, sb, r, row, slab, retired); ++w5; break;
-            default:        interact_track<R, P_ANNIH>(d, s, sb, r, row, slab, retired); ++w6; break;
-            }
+            const int proc = a - A_PROC0;
+            interact_track<R>(d, proc, s, d.type[s], sb, r, row, slab, retired);
+            w0 += proc == P_COMPTON;
+            w1 += proc == P_PHOTO;
+            w2 += proc == P_PAIR;
+            w3 += proc == P_MOLLER;
+            w4 += proc == P_BHABHA;
+            w5 += proc == P_BREMS;
+            w6 += proc == P_ANNIH;
         }
         if (retired) reuse_acc += reuse_slot(d, s, sb, row, slab, r);
         append_secondaries<R, DET>(d, sb, row, slab, r, retired != 0, off + i);
@@ -1750,189 +1800,451 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact_all(Dev<R> d)
     flush_count_shared(d, W_REUSE, reuse_acc);
 }
 
-// ---- drain: block-local stepping of the last tracks ---------------------------------
-// When few tracks are left the step loop is bound by per-iteration launch
-// latency, not by work.  A drain launch steps them without further launches:
-// each block runs its own small step loop in rounds.  Half of a block's
-// threads own occupied slots, half own vacant ones; in every round each
-// thread with a track takes up to kDrainBurst steps -- pre-step, along-step
-// and interaction, through the same per-track functions as the action
-// kernels -- and the secondaries go onto the block's stack (LIFO); at the
-// start of the next round the threads whose slot is vacant take the newest
-// entries.  A sub-shower so spreads over the block's threads instead of one
-// thread stepping it alone.  A thread knows from its own steps whether its
-// slot holds a track (a step that retires the track says so), so a round
-// reads no slot state beyond what the steps read; several steps per round
-// spread the round's barriers over them, which matters at the end, when a
-// few long-lived tracks are left.
-// After `max_steps` rounds, or when a block has neither tracks nor entries,
-// the block stops; its stack entries (and any that did not fit) go to the
-// initializer buffer for the step loop.  Random numbers are keyed by track
-// and step, so every track ends exactly as in the step loop.
+// ---- block-local step loops -----------------------------------------------------
+// One launch runs several step iterations: each block owns a share of the
+// track slots (in chunks of 64, chunk c to block c mod blocks) and steps their
+// tracks by itself, so that an iteration needs no launches, no global scan of
+// vacancies, no sort of the slots and no trip through the initializer buffer.
+//
+// A step is cut into the parts below, and every slot has a state byte in LDS:
+// its particle type and the part its track waits for.  The block works in
+// rounds: it lists its slots by state, then its waves take chunks of 64 slots
+// that wait for the same part until the lists are done.  So every wave runs
+// one part's code with all of its lanes, where a step in one piece keeps a
+// wave busy until its slowest lane has crossed a boundary, chosen a process
+// and ended, and no wave waits for another part to end.  While there are
+// chunks enough for all waves, a list's last, partial chunk waits for the
+// next round to fill up.
+//
+// Random numbers are keyed by track and step, so every track ends exactly as
+// with the kernels of a step iteration.  New tracks start in the block's
+// vacant slots, wait on its stack, or go to the initializer buffer, from
+// which the next fill spreads them over all blocks.
+constexpr int kStepsThreads = 512;
+constexpr uint32_t kStepsSlots = 8192;       // most slots of a block
 
-// Secondaries of one step onto the block's stack while it has room (`top`
-// counts its entries, in LDS), else to the initializer buffer.
-template <class R>
-__device__ __forceinline__ void drain_push(const Dev<R>& d, const SecBuf<R>& sb, uint32_t row, uint16_t slab,
-                                           const double r[3], Initializer* bstack, int cap, int* top, bool retiring)
+// parts (lists), in the order in which a round's chunks are taken: long ones first
+enum : int {
+    L_PROC0 = 0,                     // + process: the interaction
+    L_REST = L_PROC0 + kNumProc,     // field step: the RK4 evaluations after the first
+    L_SELECT,                        // choice of the process of a step that ended in an interaction
+    L_CHARGED_NEW,                   // pre-step and step (in a field: its first RK4 evaluation), the
+    L_CHARGED,                       //   interaction length drawn first, or left from the last step
+    L_PHOTON_NEW,                    // the same for photons
+    L_PHOTON,
+    L_WORK,                          // lists that hold work
+    L_VACANT = L_WORK,
+    L_NUM
+};
+static_assert(L_NUM <= 16, "counters of a round");
+// State byte of a slot: the list it is in << 2 | the particle type.  (Tracks
+// that draw an interaction length are listed apart from those that have one
+// left: the draw is the dearest part of a pre-step, and a wave skips it only
+// if none of its tracks needs it.)
+__device__ __forceinline__ uint8_t state_of(int typ, int list) { return (uint8_t)(list << 2 | typ); }
+// ready for its next step; `drawn`: with an interaction length left
+__device__ __forceinline__ uint8_t ready(int typ, bool drawn)
 {
-    // the event's counters change once per track, as in append_secondaries
-    const int dlive = sb.n - (retiring ? 1 : 0);
-    if (dlive != 0) atomicAdd(live_of(d, row), (unsigned int)dlive);    // modulo 2^32: a decrement for -1
-    if (sb.n == 0) return;
-    const int pos = atomicAdd(top, sb.n);
-    unsigned int n_gam = 0, n_ele = 0, n_pos = 0;
-    sb.each([&](const Sec<R>& v, int k) {
-        Initializer rec;
-        rec.T = (double)v.T;
-        rec.r[0] = r[0]; rec.r[1] = r[1]; rec.r[2] = r[2];
-        rec.u[0] = (double)v.ux; rec.u[1] = (double)v.uy; rec.u[2] = (double)v.uz;
-        rec.key = v.key;
-        rec.row = row;
-        rec.slab = slab;
-        rec.type = (uint8_t)v.type;
-        rec.pad = 0;
-        n_gam += v.type == kGamma;
-        n_ele += v.type == kElectron;
-        n_pos += v.type == kPositron;
-        if (pos + k < cap) {
-            bstack[pos + k] = rec;
+    return state_of(typ, (typ == kGamma ? L_PHOTON_NEW : L_CHARGED_NEW) + (drawn ? 1 : 0));
+}
+constexpr uint8_t kVacantSlot = L_VACANT << 2 | kDead;
+constexpr uint8_t kNoSlot = 0xFF;            // a position beyond the slot array
+
+// Inclusive sums over the lanes of a full wave (row shifts, then the rows).
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
+{
+    int x = (int)v;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1, 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2, 3
+    return (uint32_t)x;
+}
+
+// List a wave's slots (up to 512: eight per lane, from position l) by state:
+// lst[place of the list + rank] = position.  `next` holds the lists' next
+// free places, wbase 16 words of the wave's own.  Per lane the eight slots
+// are counted in 4-bit fields, the wave's sums are taken on three 10-bit
+// fields a word, and one lane per list reserves the wave's places, so that a
+// round's lists cost a few hundred cycles instead of a ballot and an LDS
+// round trip per list and 64 slots (14 000 cycles a round for 4096 slots).
+__device__ __forceinline__ void list_slots(const uint8_t* state, uint32_t l, uint32_t per_block, uint16_t* lst,
+                                           uint32_t* next, uint32_t* wbase)
+{
+    constexpr int NW = (L_NUM + 2) / 3;
+    static_assert(L_NUM <= 15, "4-bit fields of the lists (and one for no slot)");
+    const uint64_t st = l < per_block ? *reinterpret_cast<const uint64_t*>(state + l) : ~0ull;
+    uint64_t h = 0, rank = 0;
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t b = (uint32_t)(st >> (8 * k)) & 0xFFu, f = b == kNoSlot ? 60u : (b >> 2) * 4;
+        rank |= ((h >> f) & 15u) << (8 * k);
+        h += 1ull << f;
+    }
+    uint32_t sum[NW], mine[NW];
+    for (int q = 0; q < NW; ++q) {
+        mine[q] = 0;
+        for (int e = 0; e < 3 && 3 * q + e < L_NUM; ++e)
+            mine[q] |= ((uint32_t)(h >> (4 * (3 * q + e))) & 15u) << (10 * e);
+        sum[q] = wave_scan(mine[q]);
+    }
+    const int lane = lane_id();
+    uint32_t tot = 0;
+    for (int q = 0; q < NW; ++q) {
+        const uint32_t t = __builtin_amdgcn_readlane(sum[q], 63);
+        tot = lane / 3 == q ? (t >> (10 * (lane % 3))) & 1023u : tot;
+    }
+    if (lane < L_NUM) wbase[lane] = tot ? atomicAdd(&next[lane], tot) : 0u;
+    __builtin_amdgcn_wave_barrier();
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t b = (uint32_t)(st >> (8 * k)) & 0xFFu;
+        if (b == kNoSlot) continue;
+        const uint32_t c = b >> 2, q = c / 3;
+        uint32_t w = sum[0] - mine[0];
+        for (int e = 1; e < NW; ++e) w = q == (uint32_t)e ? sum[e] - mine[e] : w;
+        const uint32_t at = wbase[c] + ((w >> (10 * (c % 3))) & 1023u) + ((uint32_t)(rank >> (8 * k)) & 15u);
+        lst[at] = (uint16_t)(l + k);
+    }
+}
+
+// LDS bytes of a block of `slots` slots with its tables
+constexpr size_t steps_lds(uint32_t slots, size_t tables) { return (tables + 15) / 16 * 16 + (size_t)slots * 3; }
+
+// Process of a step that ended in an interaction (A_SELECT), as the end of
+// an along-step chooses it: the same uniform, cross sections and order.
+// Without any cross section left the step ends without an interaction.
+template <class R>
+__device__ __forceinline__ uint8_t select_track(const Dev<R>& d, const Tables<R>& tb, uint32_t s, int typ,
+                                                uint32_t& row, uint32_t& retired)
+{
+    row = d.row[s];
+    const uint16_t slab = d.slab[s];
+    const TrackRec<R> tr = load_track(d, s);
+    uint32_t step = d.step[s];
+    uint8_t fl = d.flags[s];
+    const int mat = d.smat[slab];
+    R T = tr.T;
+    StepRng<R> rng(d.seed, d.row_event[row], tr.key, step, (fl & F_DREW) ? 1 : 0);
+    const R U1 = rng.next();
+    const ProcXs<R> xs = proc_xs(tb, mat, typ, T, locate(tb, T), R(d.ecut));
+    const R sig1 = total_xs(xs, typ);
+    if (sig1 > R(0)) return select_process(xs, typ, sig1, U1);
+    uint8_t na = A_IDLE;
+    d.step[s] = ++step;
+    if (step > kMaxSteps) {
+        StepTally tl = {0.0, 0, 0, 0};
+        bool alive = true;
+        guard_stop(d, row, typ, T, fl, tl, alive, na);
+        record_tally(d, row, slab, tl);
+        if (alive) {
+            d.T[s] = T;
+            d.flags[s] = fl;
         } else {
-            unsigned long long q = atomicAdd(&d.ctr->queue_size, 1ull);
-            if (q < d.queue_cap) d.queue[q] = rec;
-            else atomicOr(&d.ctr->overflow, 1u);
+            retired = step;
+            retire<R, true>(d, s, row, step);
         }
-    });
-    if (n_gam) atomicAdd(&ledger_of(d, row).n_sec[kGamma], (unsigned long long)n_gam);
-    if (n_ele) atomicAdd(&ledger_of(d, row).n_sec[kElectron], (unsigned long long)n_ele);
-    if (n_pos) atomicAdd(&ledger_of(d, row).n_sec[kPositron], (unsigned long long)n_pos);
-}
-
-// Exclusive rank of a true flag among the block's threads, and their total.
-// Contains a barrier (all threads of the block must call it).
-__device__ __forceinline__ uint32_t block_rank(bool f, uint32_t* wcnt, uint32_t& total)
-{
-    const uint64_t m = __ballot(f);
-    const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-    if (lane_id() == 0) wcnt[w] = (uint32_t)__popcll(m);
-    __syncthreads();
-    uint32_t r = rank_below(m), tot = 0;
-    for (int i = 0; i < nw; ++i) {
-        if (i < w) r += wcnt[i];
-        tot += wcnt[i];
     }
-    total = tot;
-    return r;
+    return na;
 }
 
-template <class R>
-__device__ __forceinline__ void drain_interact(const Dev<R>& d, int proc, uint32_t s, SecBuf<R>& sb, double r[3],
-                                               uint32_t& row, uint16_t& slab, uint32_t& retired)
-{
-    switch (proc) {
-    case P_COMPTON: interact_track<R, P_COMPTON>(d, s, sb, r, row, slab, retired); break;
-    case P_PHOTO:   interact_track<R, P_PHOTO>(d, s, sb, r, row, slab, retired); break;
-    case P_PAIR:    interact_track<R, P_PAIR>(d, s, sb, r, row, slab, retired); break;
-    case P_MOLLER:  interact_track<R, P_MOLLER>(d, s, sb, r, row, slab, retired); break;
-    case P_BHABHA:  interact_track<R, P_BHABHA>(d, s, sb, r, row, slab, retired); break;
-    case P_BREMS:   interact_track<R, P_BREMS>(d, s, sb, r, row, slab, retired); break;
-    default:        interact_track<R, P_ANNIH>(d, s, sb, r, row, slab, retired); break;
-    }
-}
-
-// Slots: O = the occupied ones (listed by the vacancy pass, then the
-// vacancies just filled), E = the vacancies left empty.  In block b, thread i
-// < 128 owns O[128 b + i] and thread 128 + i owns E[128 b + i] (when they
-// exist), so every block has tracks and room for their secondaries.
-template <class R>
-__global__ void __launch_bounds__(256) k_drain(Dev<R> d, const uint32_t* live_list, Initializer* stack,
-                                               uint32_t n_threads, int depth, uint32_t max_steps)
+// `per_block` slots per block (a multiple of 64, at most kStepsSlots), a
+// stack of `stack_cap` records per block.  With `sync`, tracks start new steps
+// only in rounds with no step under way, all together, `n_iter` times: every
+// track makes one step in each of n_iter iterations.  Otherwise tracks start
+// new steps in the first n_iter rounds, and the steps under way are then
+// ended.  `tail` counts the steps as drain work (the last tracks of a run),
+// else by role.
+template <class R, bool FIELD>
+__global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* stack, uint32_t stack_cap,
+                                                         uint32_t per_block, uint32_t n_iter, int sync, int tail)
 {
     extern __shared__ __align__(16) unsigned char ems_lds[];
+    __shared__ uint32_t cnt[2][16];          // slots per list: this round's, the next one's
+    __shared__ uint32_t at_list[16];         // next free entry of each list
+    __shared__ uint32_t wbase[kStepsThreads / 64][16];
+    __shared__ uint32_t next_chunk, placed;
     __shared__ int top;
-    __shared__ uint32_t wcnt[4];
-    const Tables<R> tb = block_tables(d, (R*)ems_lds);
-    const uint32_t n_old = d.ctr->alive_before;
-    const uint32_t n_take = d.ctr->n_take_q + d.ctr->n_take_p;
-    const uint32_t n_occ = n_old + n_take;
-    const uint32_t n_empty = d.ctr->n_vac - n_take;
-    const int cap = depth * (int)blockDim.x;
-    Initializer* bstack = stack + (size_t)blockIdx.x * cap;
-    const uint32_t half = blockDim.x / 2;
-    const uint32_t j = blockIdx.x * half + (threadIdx.x % half);
-    bool owns = blockIdx.x * blockDim.x + threadIdx.x < n_threads;
-    uint32_t s = 0;
-    if (threadIdx.x < half) {
-        owns = owns && j < n_occ;
-        if (owns) s = j < n_old ? live_list[j] : d.vac[j - n_old];
-    } else {
-        owns = owns && j < n_empty;
-        if (owns) s = d.vac[n_take + j];
-    }
-    unsigned long long ret_acc = 0, work = 0;
-    bool has = owns && d.type[s] != kDead;     // the thread's slot holds a track
-    if (threadIdx.x == 0) top = 0;
+    // the launch's counts (in LDS: registers are short)
+    enum { T_CHARGED = 0, T_PHOTON, T_RESUMED, T_SUB, T_PAUSED, T_INIT, T_RET, T_PROC, T_NUM = T_PROC + kNumProc };
+    __shared__ unsigned long long tot[T_NUM];
+    // the tables first (16-byte aligned end), then the lists and the states
+    Tables<R> tb = d.tb;
+    R* tab = (R*)ems_lds;
+    for (int i = threadIdx.x; i < d.n_tab; i += blockDim.x) tab[i] = d.tb.v[i];
+    tb.v = tab;
+    uint16_t* lst = (uint16_t*)(ems_lds + ((size_t)d.n_tab * sizeof(R) + 15) / 16 * 16);
+    uint8_t* state = (uint8_t*)(lst + per_block);
+    const uint32_t nt = blockDim.x, tid = threadIdx.x, nw = nt / 64;
+    const int lane = lane_id();
+    auto slot_of = [&](uint32_t l) { return blockIdx.x * per_block + l; };
+    if (tid < 32) (&cnt[0][0])[tid] = 0;
+    if (tid < T_NUM) tot[tid] = 0;
+    if (tid == 0) top = 0;
     __syncthreads();
-    for (uint32_t k = 0; k < max_steps; ++k) {
-        // threads with a vacant slot take the newest entries of the stack
-        const bool idle = owns && !has;
-        uint32_t n_idle = 0;
-        const uint32_t rank = block_rank(idle, wcnt, n_idle);
-        const int avail = top;
-        if (idle && (int)rank < avail) {
-            init_slot(d, s, bstack[avail - 1 - (int)rank]);
-            has = true;
+    for (uint32_t l = tid; l < per_block; l += nt) {
+        const uint32_t s = slot_of(l);
+        uint8_t st = kNoSlot;
+        if (s < d.n_slots) {
+            const uint8_t t = d.type[s];
+            st = t == kDead ? kVacantSlot : ready(t, !(d.nl[s] < R(0)));
+            atomicAdd(&cnt[0][st >> 2], 1u);
+        }
+        state[l] = st;
+    }
+    // tracks of a block above a quarter more than the blocks' average wait for the next fill
+    const uint32_t share = (uint32_t)((d.ctr->n_alive + d.ctr->q_base) / gridDim.x);
+    const uint32_t most = share + share / 4 + kStepsThreads;
+    Initializer* bstack = stack + (size_t)blockIdx.x * stack_cap;
+    uint32_t live0 = 0, live = 0;
+    __syncthreads();
+    uint32_t it = 0;                         // rounds (sync: iterations) in which tracks started steps
+    for (uint32_t round = 0;; ++round) {
+        const uint32_t* c = cnt[round & 1u];
+        uint32_t* c_next = cnt[(round + 1) & 1u];
+        // the lists' places and the chunks taken this round
+        uint32_t full = 0, underway = 0;
+        live = 0;
+        for (int k = 0; k < L_WORK; ++k) {
+            const uint32_t n = c[k];
+            live += n;
+            if (k < L_CHARGED_NEW) underway += n;
+            full += n / 64;
+        }
+        if (round == 0) live0 = live;
+        const int height = top;
+        if ((live == 0 && height == 0) || (it >= n_iter && underway == 0)) break;
+        const bool start = it < n_iter && (!sync || underway == 0);
+        const bool partial = sync || !start || full < 2 * nw;
+        uint32_t first[L_WORK + 1], chunk[L_WORK + 1];
+        uint32_t n_at = 0, n_chunk = 0;
+        for (int k = 0; k < L_WORK; ++k) {
+            const uint32_t n = c[k];
+            const uint32_t take = k >= L_CHARGED_NEW && !start ? 0u : (partial ? n : n & ~63u);
+            first[k] = n_at;
+            chunk[k] = n_chunk;
+            if (tid == 0) {
+                at_list[k] = n_at;
+                c_next[k] = n - take;
+            }
+            n_at += n;
+            n_chunk += (take + 63) / 64;
+        }
+        first[L_WORK] = n_at;
+        chunk[L_WORK] = n_chunk;
+        const uint32_t nv = c[L_VACANT];
+        if (tid == 0) {
+            at_list[L_VACANT] = n_at;
+            c_next[L_VACANT] = nv;
+            next_chunk = 0;
+            placed = 0;
         }
         __syncthreads();
-        if (threadIdx.x == 0) top = avail - ((int)n_idle < avail ? (int)n_idle : avail);
-        // no track left in the block: then its stack is empty too
-        if (!__syncthreads_or(has)) break;
-        for (int burst = 0; burst < kDrainBurst && has; ++burst) {
-            // the along-step functions run the pre-step (a paused step is a
-            // field step and resumes without one)
-            const uint8_t a = along_action(d, s);
-            if (a == A_NONE) {      // (every retirement is reported; kept as a guard)
-                has = false;
-                break;
+        for (uint32_t base = 0; base < per_block; base += 8 * nt)
+            list_slots(state, base + 8 * tid, per_block, lst, at_list, wbase[tid / 64]);
+        __syncthreads();
+        const uint16_t* vac = lst + n_at;
+        const uint32_t room = most > live ? most - live : 0u;
+        uint32_t avail = nv < room ? nv : room;
+        // the newest records of the stack start first
+        uint32_t refill = 0;
+        if (height > 0) {
+            refill = avail < (uint32_t)height ? avail : (uint32_t)height;
+            for (uint32_t i = tid; i < refill; i += nt) {
+                const uint32_t l = vac[avail - 1 - i];
+                const Initializer rec = bstack[height - 1 - (int)i];
+                init_slot<R, true>(d, slot_of(l), rec);
+                const uint8_t st = ready(rec.type, false);
+                state[l] = st;
+                atomicAdd(&c_next[st >> 2], 1u);
             }
+            __syncthreads();
+            if (tid == 0) {
+                top = height - (int)refill;
+                c_next[L_VACANT] -= refill;
+                tot[T_INIT] += refill;
+            }
+            avail -= refill;
+            __syncthreads();
+        }
+        auto go = [&](uint32_t l, uint8_t st) {
+            state[l] = st;
+            atomicAdd(&c_next[st >> 2], 1u);
+        };
+        auto end_track = [&](uint32_t l, uint32_t row, uint32_t steps) {
+            go(l, kVacantSlot);
+            leave_event(d, true, row);
+            atomicAdd(&tot[T_RET], (unsigned long long)steps);
+        };
+        for (;;) {
+            uint32_t j = 0;
+            if (lane == 0) j = atomicAdd(&next_chunk, 1u);
+            j = __builtin_amdgcn_readfirstlane(j);
+            if (j >= n_chunk) break;
+            int k = 0;
+            uint32_t at = 0, end = 0;
+            for (int q = 0; q < L_WORK; ++q)
+                if (j >= chunk[q] && j < chunk[q + 1]) {
+                    k = q;
+                    at = first[q] + (j - chunk[q]) * 64;
+                    end = first[q + 1];
+                }
+            k = __builtin_amdgcn_readfirstlane(k);
+            const uint32_t i = at + (uint32_t)lane;
+            const bool act = i < end;
+            const uint32_t l = act ? lst[i] : 0u;
+            const uint32_t s = slot_of(l);
+            const int typ = state[l] & 3;
             uint32_t row = 0, retired = 0;
             uint8_t next = A_NONE;
-            if (a == A_NEUTRAL) {
-                along_straight_track<R, false>(d, tb, s, row, next, retired);
-            } else if (a == A_CHARGED) {
-                along_straight_track<R, true>(d, tb, s, row, next, retired);
-            } else {
-                // a paused step resumes at the thread's next step (pausing does not change the result)
+            if (k == L_CHARGED_NEW || k == L_CHARGED) {
+                if (!act) continue;
                 uint32_t att = 0, paused_n = 0, pre_n = 0;
-                along_field_track<R>(d, tb, s, kDrainSubsteps, row, next, retired, att, paused_n, pre_n);
-            }
-            if (next >= A_PROC0 && next < A_NUM) {
+                bool resumed = false;
+                if (FIELD) {
+                    FieldIn<R> in;
+                    load_field_in(d, s, (uint8_t)typ, in);
+                    resumed = (in.fl & F_PAUSED) != 0;
+                    if (!resumed)
+                        along_field_track<R, true, STEP_FIRST>(d, tb, s, in, 1, row, next, retired, att, paused_n, pre_n);
+                } else {
+                    along_straight_track<R, true, true>(d, tb, s, typ, row, next, retired);
+                }
+                if (retired) {
+                    end_track(l, row, retired);
+                } else if (next == A_SELECT) {
+                    go(l, state_of(typ, L_SELECT));
+                } else if (next == A_ANNIH) {
+                    go(l, state_of(typ, L_PROC0 + P_ANNIH));
+                } else if (resumed || (paused_n && d.max_substeps != 1)) {
+                    go(l, state_of(typ, L_REST));
+                    if (resumed) atomicAdd(&tot[T_RESUMED], 1ull);
+                } else {
+                    go(l, ready(typ, true));
+                    if (paused_n) atomicAdd(&tot[T_PAUSED], 1ull);
+                }
+            } else if (k == L_PHOTON_NEW || k == L_PHOTON) {
+                if (!act) continue;
+                along_straight_track<R, false, true>(d, tb, s, kGamma, row, next, retired);
+                if (retired) end_track(l, row, retired);
+                else go(l, next == A_SELECT ? state_of(kGamma, L_SELECT) : ready(kGamma, true));
+            } else if (k == L_SELECT) {
+                if (!act) continue;
+                next = select_track<R>(d, tb, s, typ, row, retired);
+                if (retired) end_track(l, row, retired);
+                else go(l, next >= A_PROC0 && next < A_NUM ? state_of(typ, next - A_PROC0 + L_PROC0)
+                                                                : ready(typ, false));
+            } else if (k == L_REST) {
+                if (!FIELD || !act) continue;
+                // the first evaluation counts toward the iteration's cap
+                const uint32_t att0 = d.max_substeps == 1 ? 0u : 1u;
+                uint32_t att = att0, paused_n = 0, pre_n = 0;
+                FieldIn<R> in;
+                load_field_in(d, s, (uint8_t)typ, in);
+                along_field_track<R, true, STEP_REST>(d, tb, s, in, d.max_substeps, row, next, retired, att, paused_n,
+                                                      pre_n);
+                atomicAdd(&tot[T_SUB], (unsigned long long)(att - att0));
+                if (retired) end_track(l, row, retired);
+                else if (next == A_SELECT) go(l, state_of(typ, L_SELECT));
+                else if (next == A_ANNIH) go(l, state_of(typ, L_PROC0 + P_ANNIH));
+                else go(l, ready(typ, true));
+                if (paused_n) atomicAdd(&tot[T_PAUSED], 1ull);
+            } else {
+                if (!act) continue;
                 SecBuf<R> sb;
                 sb.n = 0;
                 double r[3] = {0.0, 0.0, 0.0};
                 uint16_t slab = 0;
-                drain_interact<R>(d, next - A_PROC0, s, sb, r, row, slab, retired);
-                drain_push(d, sb, row, slab, r, bstack, cap, &top, retired != 0);
-            } else if (retired) {
-                leave_event(d, true, row);
+                interact_track<R, true>(d, k - L_PROC0, s, typ, sb, r, row, slab, retired);
+                go(l, retired ? kVacantSlot : ready(typ, false));
+                if (retired) atomicAdd(&tot[T_RET], (unsigned long long)retired);
+                unsigned int n_gam = 0, n_ele = 0, n_pos = 0;
+                sb.each([&](const Sec<R>& v, int) {
+                    n_gam += v.type == kGamma;
+                    n_ele += v.type == kElectron;
+                    n_pos += v.type == kPositron;
+                });
+                count_secondaries(d, row, n_gam, n_ele, n_pos, retired != 0);
+                // secondaries: a vacant slot, the stack, or the initializer buffer
+                // (a run-time loop over the buffer's entries: one copy of the code)
+                const uint32_t at0 = sb.n > 0 ? atomicAdd(&placed, (uint32_t)sb.n) : 0u;
+#pragma unroll 1
+                for (int q = 0; q < sb.n; ++q) {
+                    const Sec<R> v = {q == 0 ? sb.s0.T : (q == 1 ? sb.s1.T : sb.s2.T),
+                                      q == 0 ? sb.s0.ux : (q == 1 ? sb.s1.ux : sb.s2.ux),
+                                      q == 0 ? sb.s0.uy : (q == 1 ? sb.s1.uy : sb.s2.uy),
+                                      q == 0 ? sb.s0.uz : (q == 1 ? sb.s1.uz : sb.s2.uz),
+                                      q == 0 ? sb.s0.key : (q == 1 ? sb.s1.key : sb.s2.key),
+                                      q == 0 ? sb.s0.type : (q == 1 ? sb.s1.type : sb.s2.type)};
+                    const Initializer rec = secondary_record(v, r, row, slab);
+                    if (at0 + (uint32_t)q < avail) {
+                        const uint32_t l2 = vac[at0 + (uint32_t)q];
+                        init_slot<R, true>(d, slot_of(l2), rec);
+                        go(l2, ready(rec.type, false));
+                        continue;
+                    }
+                    const int pos = atomicAdd(&top, 1);
+                    if (pos < (int)stack_cap) {
+                        bstack[pos] = rec;
+                        continue;
+                    }
+                    const unsigned long long b = atomicAdd(&d.ctr->queue_size, 1ull);
+                    if (b < d.queue_cap) d.queue[b] = rec;
+                    else atomicOr(&d.ctr->overflow, 1u);
+                }
             }
-            ret_acc += retired;
-            ++work;
-            has = retired == 0;     // a retired track has left its slot
         }
         __syncthreads();
-        if (threadIdx.x == 0 && top > cap) top = cap;     // the excess went to the initializer buffer
+        if (tid == 0) {
+            const uint32_t used = placed < avail ? placed : avail;
+            c_next[L_VACANT] -= used;
+            tot[T_INIT] += used;
+            if (top > (int)stack_cap) top = (int)stack_cap;
+            if (start) {
+                for (int k = L_CHARGED_NEW; k <= L_PHOTON; ++k)
+                    tot[k <= L_CHARGED ? T_CHARGED : T_PHOTON] += partial ? c[k] : c[k] & ~63u;
+            }
+            for (int p = 0; p < kNumProc; ++p) tot[T_PROC + p] += partial ? c[L_PROC0 + p] : c[L_PROC0 + p] & ~63u;
+        }
+        it += start ? 1u : 0u;
         __syncthreads();
     }
-    // what is left on the stack goes back to the step loop
-    const int left = top;
-    for (int i = threadIdx.x; i < left; i += blockDim.x) {
-        unsigned long long q = atomicAdd(&d.ctr->queue_size, 1ull);
-        if (q < d.queue_cap) d.queue[q] = bstack[i];
-        else atomicOr(&d.ctr->overflow, 1u);
+    // the slots' types, and no action (the along-steps set every live track's)
+    for (uint32_t l = tid; l < per_block; l += nt) {
+        const uint32_t s = slot_of(l);
+        if (s >= d.n_slots) continue;
+        d.type[s] = state[l] & 3;
+        d.action[s] = state[l] == kVacantSlot ? A_NONE : A_IDLE;
     }
-    flush_count(d, W_DRAIN, work);
-    flush_count(d, kStepsSlot + W_DRAIN, ret_acc);
+    const uint32_t left = (uint32_t)top;
+    if (left > 0) {
+        __shared__ unsigned long long qbase;
+        if (tid == 0) qbase = atomicAdd(&d.ctr->queue_size, (unsigned long long)left);
+        __syncthreads();
+        for (uint32_t i = tid; i < left; i += nt) {
+            if (qbase + i < d.queue_cap) d.queue[qbase + i] = bstack[i];
+            else atomicOr(&d.ctr->overflow, 1u);
+        }
+    }
+    if (tid != 0) return;
+    // live tracks at the end of the launch
+    if (live != live0) atomicAdd(&d.ctr->n_alive, (unsigned int)(live - live0));
+    auto add = [&](int role, unsigned long long v) {
+        if (v) d.part[(size_t)role * d.part_stride + blockIdx.x] += v;
+    };
+    const unsigned long long n_charged = tot[T_CHARGED], n_photon = tot[T_PHOTON], n_new = n_charged - tot[T_RESUMED];
+    add(kStepsSlot + W_DRAIN, tot[T_RET]);
+    if (tail) {
+        add(W_DRAIN, n_charged + n_photon);
+        return;
+    }
+    add(FIELD ? W_FIELD : W_CHARGED, n_charged);
+    add(W_NEUTRAL, n_photon);
+    add(W_PRE, n_new + n_photon);
+    if (FIELD) add(W_SUBSTEPS, n_new + tot[T_SUB]);
+    add(W_PAUSED, tot[T_PAUSED]);
+    add(W_INIT, tot[T_INIT]);
+    for (int p = 0; p < kNumProc; ++p) add(W_PROC0 + p, tot[T_PROC + p]);
 }
 
 // ---- event completion ---------------------------------------------------------------

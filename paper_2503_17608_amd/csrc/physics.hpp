@@ -39,14 +39,17 @@ struct Loc {
 template <class R>
 __device__ __forceinline__ Loc<R> locate(const Tables<R>& tb, R T)
 {
-    R t = (m_log(T) - tb.ln_e0) * tb.inv_dlog;
+    const R x = m_log(T) - tb.ln_e0;
+    R t = x * tb.inv_dlog;
     R fl = m_floor(t);
     int i = (int)fl;
     if (fl < R(0)) i = 0;
     if (fl > R(kNodes - 2)) i = kNodes - 2;
     Loc<R> l;
     l.i = i;
-    l.f = t - R(i);
+    // written as the fused operation, which the compiler makes of t - i where
+    // it sees both, so that every use gets the same bits
+    l.f = m_fma(x, tb.inv_dlog, -R(i));
     return l;
 }
 
@@ -55,20 +58,6 @@ __device__ __forceinline__ R interp(const R* v, const Loc<R>& l)
 {
     R a = v[l.i], b = v[l.i + 1];
     return a + l.f * (b - a);
-}
-
-// macroscopic cross section of process p at T, zero at and below its threshold
-template <class R>
-__device__ __forceinline__ R proc_xs(const Tables<R>& tb, int mat, int p, R T, const Loc<R>& l, R ecut)
-{
-    switch (p) {
-    case P_COMPTON: return interp(tb.tab(mat, TB_COMPTON), l);
-    case P_PHOTO:   return interp(tb.tab(mat, TB_PHOTO), l);
-    case P_PAIR:    return T <= R(2.0 * kMe) ? R(0) : interp(tb.tab(mat, TB_PAIR), l);
-    case P_MOLLER:  return T <= R(2) * ecut ? R(0) : interp(tb.tab(mat, TB_MOLLER), l);
-    case P_BHABHA:  return T <= ecut ? R(0) : interp(tb.tab(mat, TB_BHABHA), l);
-    default:        return T <= ecut ? R(0) : interp(tb.tab(mat, TB_BREMS), l);
-    }
 }
 
 // processes of each particle, in selection order
@@ -80,12 +69,39 @@ __device__ __forceinline__ int proc_of(int type, int n)
     return n == 0 ? P_BHABHA : P_BREMS;
 }
 
+// Macroscopic cross sections of a particle's processes at T, in selection
+// order, zero at and below their thresholds.  Every table is read whatever
+// the thresholds say, so that the loads are in flight together.
 template <class R>
-__device__ __forceinline__ R total_xs(const Tables<R>& tb, int mat, int type, R T, const Loc<R>& l, R ecut)
+struct ProcXs {
+    R x[3];       // [2]: photons only
+};
+
+template <class R>
+__device__ __forceinline__ ProcXs<R> proc_xs(const Tables<R>& tb, int mat, int typ, R T, const Loc<R>& l, R ecut)
 {
-    R s = R(0);
-    for (int n = 0; n < n_proc(type); ++n) s += proc_xs(tb, mat, proc_of(type, n), T, l, ecut);
+    ProcXs<R> s;
+    if (typ == kGamma) {
+        s.x[0] = interp(tb.tab(mat, TB_COMPTON), l);
+        s.x[1] = interp(tb.tab(mat, TB_PHOTO), l);
+        const R pair = interp(tb.tab(mat, TB_PAIR), l);
+        s.x[2] = T <= R(2.0 * kMe) ? R(0) : pair;
+    } else {
+        const bool ele = typ == kElectron;
+        const R delta = interp(tb.tab(mat, ele ? TB_MOLLER : TB_BHABHA), l);
+        const R brems = interp(tb.tab(mat, TB_BREMS), l);
+        s.x[0] = T <= (ele ? R(2) * ecut : ecut) ? R(0) : delta;
+        s.x[1] = T <= ecut ? R(0) : brems;
+        s.x[2] = R(0);
+    }
     return s;
+}
+
+template <class R>
+__device__ __forceinline__ R total_xs(const ProcXs<R>& s, int typ)
+{
+    const R two = s.x[0] + s.x[1];
+    return typ == kGamma ? two + s.x[2] : two;
 }
 
 template <class R>
@@ -96,19 +112,32 @@ __device__ __forceinline__ const R* range_tab(const Tables<R>& tb, int mat, int 
 
 // Exact inverse of the piecewise-linear range map: the interval is the one an
 // upper-bound search on the node ranges finds (first node with R > r, minus
-// one); ln T is linear in R inside it.  The search walks down from a starting
-// node `j0` (the interval of the pre-step energy, since r <= R(T)), which
-// finds the same interval as a binary search in one or two probes.
+// one); ln T is linear in R inside it.  The search starts at interval i0 of
+// the pre-step energy; a step loses at most a fifth of the range (below the
+// final range more), so the interval is i0 or one of the two below, whose
+// nodes are read together; else it walks on from i0 node by node.
 template <class R>
-__device__ __forceinline__ R inverse_range(const Tables<R>& tb, const R* Rt, R r, int j0)
+__device__ __forceinline__ R inverse_range(const Tables<R>& tb, const R* Rt, R r, int i0)
 {
-    int j = j0 < kNodes ? j0 : kNodes;
-    while (j < kNodes && !(Rt[j] > r)) ++j;
-    while (j > 0 && Rt[j - 1] > r) --j;
-    int i = j - 1;
-    if (i < 0) i = 0;
-    if (i > kNodes - 2) i = kNodes - 2;
-    R t = R(i) + (r - Rt[i]) / (Rt[i + 1] - Rt[i]);
+    const R r1 = Rt[i0 + 1], r0 = Rt[i0], rm = Rt[i0 > 0 ? i0 - 1 : 0], rn = Rt[i0 > 1 ? i0 - 2 : 0];
+    int i = i0;
+    R lo = r0, hi = r1;
+    if (!(r1 > r) || (r0 > r && !(i0 > 0 && !(rm > r)) && !(i0 > 1 && !(rn > r)))) {
+        int j = i0 + 1;
+        while (j < kNodes && !(Rt[j] > r)) ++j;
+        while (j > 0 && Rt[j - 1] > r) --j;
+        i = j - 1;
+        if (i < 0) i = 0;
+        if (i > kNodes - 2) i = kNodes - 2;
+        lo = Rt[i];
+        hi = Rt[i + 1];
+    } else if (r0 > r) {
+        const bool one = !(rm > r);
+        i = one ? i0 - 1 : i0 - 2;
+        lo = one ? rm : rn;
+        hi = one ? r0 : rm;
+    }
+    R t = R(i) + (r - lo) / (hi - lo);
     return m_exp(tb.ln_e0 + t * tb.dlog);
 }
 
@@ -228,183 +257,197 @@ struct Prim {
     bool alive;
 };
 
-// the lepton stops: deposit its kinetic energy; positrons annihilate
+// The lepton stops: its kinetic energy is deposited; a positron annihilates.
+// Returns true when its annihilation at rest is still to be done.
 template <class R>
-__device__ __forceinline__ void stop_lepton(const PhysParams& pp, Prim<R>& t, SecBuf<R>& sb, StepTally& tl)
+__device__ __forceinline__ bool stop_lepton(Prim<R>& t, StepTally& tl)
 {
     tl.edep += (double)t.T;
-    if (t.type == kPositron) annihilate<R>(pp, t.key, t.step, sb, tl);
     t.T = R(0);
     t.alive = false;
+    return t.type == kPositron;
 }
 
+// Sampled variable of process `proc` for a track of kinetic energy T (or a
+// photon's energy): Compton's energy ratio, the pair's electron share, the
+// delta ray's share of T, the photon's share of E.  One trial loop for all of
+// them, so that the drawing of the uniforms is in the code once.
 template <class R>
-__device__ __forceinline__ void sample_compton(const PhysParams& pp, Prim<R>& t, StepRng<R>& rng, SecBuf<R>& sb, StepTally& tl)
+__device__ __forceinline__ R sample_share(int proc, R T, R ec, StepRng<R>& rng, StepTally& tl)
 {
-    const R ec = R(pp.ecut);
-    R E = t.T, kap = E / R(kMe);
-    R e0 = R(1) / (R(1) + R(2) * kap), e0sq = e0 * e0;
-    R a1 = -m_log(e0), a2 = R(0.5) * (R(1) - e0sq);
-    R eps = R(1), omc = R(0);
+    R c0 = R(0), c1 = R(0), c2 = R(0), c3 = R(0), c4 = R(0), c5 = R(0);
+    // (sums of products that several branches use are written as fused
+    // operations: whether the compiler fuses one depends on the code around it)
+    if (proc == P_COMPTON) {                    // kappa, e0^2, a1, a2, 1 - e0^2
+        const R kap = T / R(kMe);
+        const R e0 = R(1) / (R(1) + R(2) * kap), e0sq = e0 * e0;
+        c0 = kap;
+        c1 = e0sq;
+        c2 = -m_log(e0);
+        c4 = m_fma(-e0, e0, R(1));
+        c3 = R(0.5) * c4;
+    } else if (proc == P_PAIR) {                // m / E
+        c0 = R(kMe) / T;
+    } else if (proc == P_MOLLER) {              // cut / T, C1, C2, bound
+        const R g = (T + R(kMe)) / R(kMe);
+        c0 = ec / T;
+        c1 = ((g - R(1)) / g) * ((g - R(1)) / g);
+        c2 = (R(2) * g - R(1)) / (g * g);
+        c3 = R(1) + c1 / R(4) + m_max(R(0), R(1) - c2);
+    } else if (proc == P_BHABHA) {              // cut / T, beta^2, B1..B4
+        const R g = (T + R(kMe)) / R(kMe);
+        const R y = R(1) / (R(1) + g);
+        c0 = ec / T;
+        c1 = R(1) - R(1) / (g * g);
+        c2 = R(2) - y * y;
+        c3 = (R(1) - R(2) * y) * (R(3) + y * y);
+        c5 = (R(1) - R(2) * y) * (R(1) - R(2) * y) * (R(1) - R(2) * y);
+        c4 = c5 + (R(1) - R(2) * y) * (R(1) - R(2) * y);
+    } else {                                    // cut / E, ln(T / cut)
+        const R E = T + R(kMe);
+        c0 = ec / E;
+        c1 = m_log((T / E) / c0);
+    }
+    R x = R(0);
+    const int n = proc == P_COMPTON ? 3 : 2;
     for (int trial = 0; trial < kMaxTrials; ++trial) {
-        R a = rng.next(), b = rng.next(), c = rng.next();
-        if (a * (a1 + a2) < a1) eps = m_exp(-a1 * b);
-        else eps = m_sqrt(e0sq + (R(1) - e0sq) * b);
-        omc = (R(1) - eps) / (kap * eps);
-        R sin2 = omc * (R(2) - omc);
-        R g = R(1) - eps * sin2 / (R(1) + eps * eps);
-        if (c <= g) break;
+        R a = R(0), b = R(0), c = R(0);          // the trial's uniforms, the last ones in b and c
+#pragma unroll 1
+        for (int k = 0; k < n; ++k) {
+            a = b;
+            b = c;
+            c = rng.next();
+        }
+        bool ok;
+        if (proc == P_COMPTON) {
+            if (a * (c2 + c3) < c2) x = m_exp(-c2 * b);
+            else x = m_sqrt(m_fma(c4, b, c1));
+            const R omc = (R(1) - x) / (c0 * x);
+            const R sin2 = omc * (R(2) - omc);
+            ok = c <= R(1) - x * sin2 / (R(1) + x * x);
+        } else if (proc == P_PAIR) {
+            x = c0 + (R(1) - R(2) * c0) * b;
+            ok = c <= R(1) - R(4) / R(3) * x * (R(1) - x);
+        } else if (proc == P_MOLLER) {
+            x = c0 / (R(1) - b * (R(1) - R(2) * c0));
+            const R f = x * x * (c1 + R(1) / (x * x) + R(1) / ((R(1) - x) * (R(1) - x)) - c2 / (x * (R(1) - x)));
+            ok = c * c3 <= f;
+        } else if (proc == P_BHABHA) {
+            x = c0 / (R(1) - b * (R(1) - c0));
+            ok = c <= R(1) - c1 * (c2 * x - c3 * x * x + c4 * x * x * x - c5 * x * x * x * x);
+        } else {
+            x = c0 * m_exp(b * c1);
+            ok = c <= R(1) - x + R(0.75) * x * x;
+        }
+        if (ok) break;
         if (trial == kMaxTrials - 1) tl.capped = 1;
     }
-    R phi = R(2.0 * kPi) * rng.next();
-    R sp, cp;
-    m_sincos(phi, &sp, &cp);
-    R up[3];
-    rotate<R>(t.u, R(1) - omc, sp, cp, up);
-    R Ep = eps * E;
-    R Te = E - Ep;
-    if (Te >= ec) {
-        R ue[3] = {E * t.u[0] - Ep * up[0], E * t.u[1] - Ep * up[1], E * t.u[2] - Ep * up[2]};
-        normalize3(ue);
-        sb.add(kElectron, Te, ue, child_key(pp.seed, pp.event, t.key, t.step, 0));
-    } else {
-        tl.edep += (double)Te;
-    }
-    if (Ep < ec) {
-        tl.edep += (double)Ep;
+    return x;
+}
+
+// Discrete interaction `proc` of a track (P_ANNIH: at rest, the kinetic energy
+// deposited before), whose next unused uniform of the step is j0.  The
+// processes share their parts -- the trial loop, the rotation by the sampled
+// angle and the recoil, the keys of the secondaries, the annihilation -- so
+// that the code of all seven fits the instruction cache.
+template <class R>
+__device__ __forceinline__ void interact(const PhysParams& pp, int proc, Prim<R>& t, uint32_t j0, SecBuf<R>& sb,
+                                         StepTally& tl)
+{
+    const R ec = R(pp.ecut);
+    const R T = t.T;
+    const bool delta = proc == P_MOLLER || proc == P_BHABHA;
+    const uint64_t key0 = proc == P_ANNIH ? 0 : child_key(pp.seed, pp.event, t.key, t.step, 0);
+    uint64_t key_at = t.key, step_at = t.step;       // of the annihilating positron
+    bool annih = proc == P_ANNIH;
+    if (proc == P_PHOTO) {
+        if (T >= ec) sb.add(kElectron, T, t.u, key0);
+        else tl.edep += (double)T;
         t.T = R(0);
         t.alive = false;
-    } else {
-        t.T = Ep;
-        t.u[0] = up[0]; t.u[1] = up[1]; t.u[2] = up[2];
+    } else if (proc != P_ANNIH) {
+        StepRng<R> rng(pp.seed, pp.event, t.key, t.step, j0);
+        const R x = rounded(sample_share<R>(proc, T, ec, rng, tl));
+        if (proc == P_COMPTON || delta) {
+            // the scattered photon, or the delta ray, at the sampled angle about the
+            // track; the electron, or the track, takes the rest of the momentum
+            const R phi = R(2.0 * kPi) * rng.next();
+            R sp, cp;
+            m_sincos(phi, &sp, &cp);
+            R part, cosine, p_in = T, p_out;        // the sampled part of T; momenta before and of it
+            if (delta) {
+                part = x * T;
+                const R t2 = T + R(2.0 * kMe), q2 = m_fma(x, T, R(2.0 * kMe));
+                cosine = m_sqrt(part * t2 / (T * q2));
+                p_in = m_sqrt(T * t2);
+                p_out = m_sqrt(part * q2);
+            } else {
+                part = x * T;
+                cosine = R(1) - (R(1) - x) / (T / R(kMe) * x);
+                p_out = part;
+            }
+            part = rounded(part);
+            p_in = rounded(p_in);
+            p_out = rounded(p_out);
+            cosine = rounded(cosine);
+            R dir[3];
+            rotate<R>(t.u, cosine, sp, cp, dir);
+            R rest[3] = {p_in * t.u[0] - p_out * dir[0], p_in * t.u[1] - p_out * dir[1],
+                         p_in * t.u[2] - p_out * dir[2]};
+            // (the order of the squares' sum is fixed: x and y change places
+            // between the two, which is how each was rounded when on its own)
+            const R first = delta ? rest[1] : rest[0], second = delta ? rest[0] : rest[1];
+            const R norm = m_sqrt(m_fma(rest[2], rest[2], m_fma(first, first, second * second)));
+            rest[0] /= norm; rest[1] /= norm; rest[2] /= norm;
+            // what is left of T: for Compton the fused difference
+            const R left = delta ? T - part : m_fma(-x, T, T);
+            const R T_sec = delta ? part : left, T_prim = delta ? left : part;
+            for (int k = 0; k < 3; ++k) {
+                const R d0 = dir[k], d1 = rest[k];
+                dir[k] = delta ? d0 : d1;           // of the secondary
+                rest[k] = delta ? d1 : d0;          // of the track
+            }
+            if (T_sec >= ec) sb.add(kElectron, T_sec, dir, key0);
+            else tl.edep += (double)T_sec;
+            t.T = T_prim;
+            if (T_prim >= ec) {
+                t.u[0] = rest[0]; t.u[1] = rest[1]; t.u[2] = rest[2];
+            } else {
+                annih = stop_lepton<R>(t, tl);      // (a photon: deposited like a lepton)
+            }
+        } else if (proc == P_PAIR) {
+            const R Tp = m_fma(x, T, -R(kMe)), Tm = m_fma(R(1) - x, T, -R(kMe));
+            if (Tm >= ec) sb.add(kElectron, Tm, t.u, key0);
+            else tl.edep += (double)Tm;
+            const uint64_t kp = child_key(pp.seed, pp.event, t.key, t.step, 1);
+            if (Tp >= ec) {
+                sb.add(kPositron, Tp, t.u, kp);
+            } else {
+                // a positron below the cut is not tracked: it deposits and annihilates
+                // at the vertex with its own key at step 0
+                tl.edep += (double)Tp;
+                annih = true;
+                key_at = kp;
+                step_at = 0;
+            }
+            tl.n_pair += 1;
+            t.T = R(0);
+            t.alive = false;
+        } else {                                    // bremsstrahlung
+            const R k = rounded(x * (T + R(kMe)));
+            if (k >= ec) sb.add(kGamma, k, t.u, key0);
+            else tl.edep += (double)k;
+            t.T = T - k;
+            if (t.T < ec) annih = stop_lepton<R>(t, tl);
+        }
     }
-}
-
-template <class R>
-__device__ __forceinline__ void sample_photo(const PhysParams& pp, Prim<R>& t, SecBuf<R>& sb, StepTally& tl)
-{
-    R Te = t.T;
-    if (Te >= R(pp.ecut)) sb.add(kElectron, Te, t.u, child_key(pp.seed, pp.event, t.key, t.step, 0));
-    else tl.edep += (double)Te;
-    t.T = R(0);
-    t.alive = false;
-}
-
-template <class R>
-__device__ __forceinline__ void sample_pair(const PhysParams& pp, Prim<R>& t, StepRng<R>& rng, SecBuf<R>& sb, StepTally& tl)
-{
-    const R ec = R(pp.ecut);
-    R E = t.T, a = R(kMe) / E, x = R(0.5);
-    for (int trial = 0; trial < kMaxTrials; ++trial) {
-        x = a + (R(1) - R(2) * a) * rng.next();
-        R acc = rng.next();
-        if (acc <= R(1) - R(4) / R(3) * x * (R(1) - x)) break;
-        if (trial == kMaxTrials - 1) tl.capped = 1;
+    if (annih) {
+        annihilate<R>(pp, key_at, step_at, sb, tl);
+        if (proc == P_ANNIH) {
+            t.T = R(0);
+            t.alive = false;
+        }
     }
-    R Tp = x * E - R(kMe), Tm = (R(1) - x) * E - R(kMe);
-    if (Tm >= ec) sb.add(kElectron, Tm, t.u, child_key(pp.seed, pp.event, t.key, t.step, 0));
-    else tl.edep += (double)Tm;
-    uint64_t kp = child_key(pp.seed, pp.event, t.key, t.step, 1);
-    if (Tp >= ec) {
-        sb.add(kPositron, Tp, t.u, kp);
-    } else {
-        // a positron below the cut is not tracked: it deposits and annihilates
-        // at the vertex with its own key at step 0
-        tl.edep += (double)Tp;
-        annihilate<R>(pp, kp, 0, sb, tl);
-    }
-    tl.n_pair += 1;
-    t.T = R(0);
-    t.alive = false;
-}
-
-template <class R>
-__device__ __forceinline__ void delta_final(const PhysParams& pp, Prim<R>& t, R eps, StepRng<R>& rng, SecBuf<R>& sb, StepTally& tl)
-{
-    const R ec = R(pp.ecut);
-    R T = t.T;
-    R phi = R(2.0 * kPi) * rng.next();
-    R sp, cp;
-    m_sincos(phi, &sp, &cp);
-    R Td = eps * T;
-    R cosd = m_sqrt(Td * (T + R(2.0 * kMe)) / (T * (Td + R(2.0 * kMe))));
-    R ud[3];
-    rotate<R>(t.u, cosd, sp, cp, ud);
-    R p = m_sqrt(T * (T + R(2.0 * kMe))), pd = m_sqrt(Td * (Td + R(2.0 * kMe)));
-    R un[3] = {p * t.u[0] - pd * ud[0], p * t.u[1] - pd * ud[1], p * t.u[2] - pd * ud[2]};
-    R Tn = T - Td;
-    if (Td >= ec) sb.add(kElectron, Td, ud, child_key(pp.seed, pp.event, t.key, t.step, 0));
-    else tl.edep += (double)Td;
-    t.T = Tn;
-    if (Tn < ec) {
-        stop_lepton<R>(pp, t, sb, tl);
-    } else {
-        normalize3(un);
-        t.u[0] = un[0]; t.u[1] = un[1]; t.u[2] = un[2];
-    }
-}
-
-template <class R>
-__device__ __forceinline__ void sample_moller(const PhysParams& pp, Prim<R>& t, StepRng<R>& rng, SecBuf<R>& sb, StepTally& tl)
-{
-    R T = t.T, xc = R(pp.ecut) / T;
-    R g = (T + R(kMe)) / R(kMe);
-    R C1 = ((g - R(1)) / g) * ((g - R(1)) / g);
-    R C2 = (R(2) * g - R(1)) / (g * g);
-    R bound = R(1) + C1 / R(4) + m_max(R(0), R(1) - C2);
-    R eps = R(0.5);
-    for (int trial = 0; trial < kMaxTrials; ++trial) {
-        eps = xc / (R(1) - rng.next() * (R(1) - R(2) * xc));
-        R acc = rng.next();
-        R f = eps * eps * (C1 + R(1) / (eps * eps) + R(1) / ((R(1) - eps) * (R(1) - eps)) - C2 / (eps * (R(1) - eps)));
-        if (acc * bound <= f) break;
-        if (trial == kMaxTrials - 1) tl.capped = 1;
-    }
-    delta_final<R>(pp, t, eps, rng, sb, tl);
-}
-
-template <class R>
-__device__ __forceinline__ void sample_bhabha(const PhysParams& pp, Prim<R>& t, StepRng<R>& rng, SecBuf<R>& sb, StepTally& tl)
-{
-    R T = t.T, xc = R(pp.ecut) / T;
-    R g = (T + R(kMe)) / R(kMe);
-    R b2 = R(1) - R(1) / (g * g);
-    R y = R(1) / (R(1) + g);
-    R B1 = R(2) - y * y;
-    R B2 = (R(1) - R(2) * y) * (R(3) + y * y);
-    R B4 = (R(1) - R(2) * y) * (R(1) - R(2) * y) * (R(1) - R(2) * y);
-    R B3 = B4 + (R(1) - R(2) * y) * (R(1) - R(2) * y);
-    R eps = R(0.5);
-    for (int trial = 0; trial < kMaxTrials; ++trial) {
-        eps = xc / (R(1) - rng.next() * (R(1) - xc));
-        R acc = rng.next();
-        R f = R(1) - b2 * (B1 * eps - B2 * eps * eps + B3 * eps * eps * eps - B4 * eps * eps * eps * eps);
-        if (acc <= f) break;
-        if (trial == kMaxTrials - 1) tl.capped = 1;
-    }
-    delta_final<R>(pp, t, eps, rng, sb, tl);
-}
-
-template <class R>
-__device__ __forceinline__ void sample_brems(const PhysParams& pp, Prim<R>& t, StepRng<R>& rng, SecBuf<R>& sb, StepTally& tl)
-{
-    const R ec = R(pp.ecut);
-    R T = t.T, E = T + R(kMe);
-    R yc = ec / E, ym = T / E;
-    R lr = m_log(ym / yc);
-    R y = yc;
-    for (int trial = 0; trial < kMaxTrials; ++trial) {
-        y = yc * m_exp(rng.next() * lr);
-        R acc = rng.next();
-        if (acc <= R(1) - y + R(0.75) * y * y) break;
-        if (trial == kMaxTrials - 1) tl.capped = 1;
-    }
-    R k = y * E;
-    if (k >= ec) sb.add(kGamma, k, t.u, child_key(pp.seed, pp.event, t.key, t.step, 0));
-    else tl.edep += (double)k;
-    R Tn = T - k;
-    t.T = Tn;
-    if (Tn < ec) stop_lepton<R>(pp, t, sb, tl);
 }
 
 }  // namespace ems

@@ -1,0 +1,107 @@
+"""Block-local step loops (partition policy, every launch fused, one stream):
+one iteration against the per-action kernels, bit for bit, and whole showers
+against the oracle where the loops can go wrong -- slot counts that end
+inside a chunk or a block, more tracks than slots (secondaries wait on the
+blocks' stacks and in the initializer buffer), tables that do not fit beside
+the lists."""
+import numpy as np
+import pytest
+
+import workloads
+from tests.gpu_helpers import assert_events_match, random_states, run_oracle, session_for, to_lib_tracks
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = {"none": (0.0, 0.0, 0.0), "x": (1.0, 0.0, 0.0), "oblique": (0.3, -0.7, 1.1)}
+LOCAL = dict(sort_policy="partition", init_partition=True, streams=1)
+WORK = ("pre_step", "along_neutral", "along_charged", "along_field", "field_paused", "field_substeps", "compton",
+        "photoelectric", "pair", "moller", "bhabha", "bremsstrahlung", "annihilation")
+
+
+def _one_iteration(w, states, slots, precision, msc, cap, local):
+    s = session_for(w, n_slots=slots, precision=precision, max_events=4, msc=msc, max_substeps=cap,
+                    n_initializers=4 * len(states), **LOCAL)
+    rows = np.array([s.register_event(10 + i) for i in range(4)], dtype=np.uint32)
+    s.inject(to_lib_tracks(states, rows[np.arange(len(states)) % 4]))
+    if local:
+        s.set_tuning(fuse_interactions=True)
+        s.step(1)
+    else:
+        s.iterate(1, no_init=True)
+    t = s.read_tracks(slots)
+    t = np.concatenate([t[t["type"] >= 0], s.read_secondaries()])
+    work = s.counters()["work"]
+    led = s.read_all()[1]
+    s.close()
+    return t[np.argsort(t["key"], kind="stable")], [work[k] for k in WORK], led
+
+
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+@pytest.mark.parametrize("field,msc,cap,n,slots", [
+    ("x", False, 10, 20000, 20000),        # no vacant slot: every secondary waits
+    ("x", True, 1, 20000, 70001),          # every step of more than one evaluation pauses
+    ("oblique", False, 0, 5000, 6143),     # no cap; the last block's slots end inside a chunk
+    ("none", True, 10, 20000, 1 << 17),    # straight charged steps
+    ("none", False, 10, 1, 1),             # one slot
+    ("x", False, 10, 65, 127),
+])
+def test_one_iteration_equals_the_action_kernels(precision, field, msc, cap, n, slots):
+    w = workloads.electron_showers_1gev_field(1)
+    w.stack = workloads.sampling_stack(50, 40.0, FIELDS[field])
+    states = random_states(w, n, np.random.default_rng(n + slots), f32=precision == "mixed")
+    ref, work_ref, led_ref = _one_iteration(w, states, slots, precision, msc, cap, False)
+    t, work, led = _one_iteration(w, states, slots, precision, msc, cap, True)
+    assert work == work_ref
+    assert np.array_equal(led, led_ref) or all(
+        np.array_equal(led[f], led_ref[f]) for f in led.dtype.names if f != "escaped")
+    assert len(t) == len(ref)
+    for f in t.dtype.names:
+        if f != "row":
+            assert np.ascontiguousarray(t[f]).tobytes() == np.ascontiguousarray(ref[f]).tobytes(), f
+
+
+@pytest.mark.parametrize("slots,drain", [(1, 0), (64, 0), (257, 0xFFFFFFFF), (1000, 0), (8191, 2048), (300001, 0)])
+def test_showers_equal_the_oracle(slots, drain):
+    w = workloads.electron_showers_1gev_field(4 if slots > 1 else 1)
+    if slots == 1:
+        w.primaries["T"] = 20.0
+    e_ref, l_ref, steps = run_oracle(w)
+    s = session_for(w, n_slots=slots, n_initializers=1 << 18, graph_iterations=8, **LOCAL)
+    s.set_tuning(fuse_interactions=True, drain_threshold=drain)
+    for _ in range(2):
+        c0 = s.counters()["steps"]
+        s.push(w.primaries)
+        c = s.run(10_000_000)
+        assert c["steps"] - c0 == steps and c["alive"] == 0 and c["queued"] == 0
+        edep, led = s.tallies_by_event(np.arange(w.n_events))
+        assert_events_match(w, edep, led, e_ref, l_ref, (slots, drain))
+        s.release(np.arange(w.n_events, dtype=np.uint64))
+    s.close()
+
+
+def test_tables_that_do_not_fit_beside_the_lists():
+    """Six materials: 70 kB of tables in FP64.  The step loops run as separate kernels that read them
+    through the caches, and the drain is left out."""
+    w = workloads.electron_showers_1gev_field(2)
+    w.stack.materials = [workloads.LEAD, workloads.LIQUID_ARGON] * 3
+    e_ref, l_ref, steps = run_oracle(w)
+    s = session_for(w, n_slots=8192, graph_iterations=4, lds_tables=0, **LOCAL)
+    s.set_tuning(fuse_interactions=True, drain_threshold=0xFFFFFFFF)
+    s.push(w.primaries)
+    c = s.run(1_000_000)
+    edep, led = s.tallies_by_event(np.arange(w.n_events))
+    s.close()
+    assert c["steps"] == steps and c["work"]["drain"] == 0 and c["work"]["along_field"] > 0
+    assert_events_match(w, edep, led, e_ref, l_ref, "six materials")
+
+
+def test_overflow_of_the_initializer_buffer_is_reported():
+    from paper_2503_17608_amd import emstep
+    w = workloads.electron_showers_1gev_field(40)
+    s = session_for(w, n_slots=64, n_initializers=8, **LOCAL)
+    s.set_tuning(fuse_interactions=True)
+    s.push(w.primaries)
+    with pytest.raises(emstep.EmsError) as e:
+        s.run(1_000_000)
+    assert e.value.status == emstep.ERR_CAPACITY
+    s.close()
