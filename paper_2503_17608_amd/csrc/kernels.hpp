@@ -1821,7 +1821,10 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact_all(Dev<R> d)
 // vacant slots, wait on its stack, or go to the initializer buffer, from
 // which the next fill spreads them over all blocks.
 constexpr int kStepsThreads = 512;
-constexpr uint32_t kStepsSlots = 8192;       // most slots of a block
+// Most slots of a block: 96 KB of lists, so that 2^23 slots still are one
+// block per CU (16 events of up to 100 GeV in 2^22 slots: 84 ms with 8192
+// slots a block and two rounds of blocks a launch, 77 ms with 16384).
+constexpr uint32_t kStepsSlots = 32768;
 
 // parts (lists), in the order in which a round's chunks are taken: long ones first
 enum : int {
@@ -1864,14 +1867,15 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t v)
 }
 
 // List a wave's slots (up to 512: eight per lane, from position l) by state:
-// lst[place of the list + rank] = position.  `next` holds the lists' next
-// free places, wbase 16 words of the wave's own.  Per lane the eight slots
+// lst[place of the list + rank] = position.  Lane k holds the first place of
+// list k; `listed` counts the places given out, wbase is 16 words of the
+// wave's own.  Per lane the eight slots
 // are counted in 4-bit fields, the wave's sums are taken on three 10-bit
 // fields a word, and one lane per list reserves the wave's places, so that a
 // round's lists cost a few hundred cycles instead of a ballot and an LDS
 // round trip per list and 64 slots (14 000 cycles a round for 4096 slots).
 __device__ __forceinline__ void list_slots(const uint8_t* state, uint32_t l, uint32_t per_block, uint16_t* lst,
-                                           uint32_t* next, uint32_t* wbase)
+                                           uint32_t first, uint32_t* listed, uint32_t* wbase)
 {
     constexpr int NW = (L_NUM + 2) / 3;
     static_assert(L_NUM <= 15, "4-bit fields of the lists (and one for no slot)");
@@ -1895,7 +1899,7 @@ __device__ __forceinline__ void list_slots(const uint8_t* state, uint32_t l, uin
         const uint32_t t = __builtin_amdgcn_readlane(sum[q], 63);
         tot = lane / 3 == q ? (t >> (10 * (lane % 3))) & 1023u : tot;
     }
-    if (lane < L_NUM) wbase[lane] = tot ? atomicAdd(&next[lane], tot) : 0u;
+    if (lane < L_NUM) wbase[lane] = first + (tot ? atomicAdd(&listed[lane], tot) : 0u);
     __builtin_amdgcn_wave_barrier();
     for (int k = 0; k < 8; ++k) {
         const uint32_t b = (uint32_t)(st >> (8 * k)) & 0xFFu;
@@ -1960,13 +1964,13 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
                                                          uint32_t per_block, uint32_t n_iter, int sync, int tail)
 {
     extern __shared__ __align__(16) unsigned char ems_lds[];
-    __shared__ uint32_t cnt[2][16];          // slots per list: this round's, the next one's
-    __shared__ uint32_t at_list[16];         // next free entry of each list
+    // by the round's parity: slots per list, places of the lists given out,
+    // chunks taken, vacancies used
+    __shared__ uint32_t cnt[2][16], listed[2][16], taken_chunks[2], placed[2];
     __shared__ uint32_t wbase[kStepsThreads / 64][16];
-    __shared__ uint32_t next_chunk, placed;
     __shared__ int top;
-    // the launch's counts (in LDS: registers are short)
-    enum { T_CHARGED = 0, T_PHOTON, T_RESUMED, T_SUB, T_PAUSED, T_INIT, T_RET, T_PROC, T_NUM = T_PROC + kNumProc };
+    // the launch's counts that single tracks add to
+    enum { T_RESUMED = 0, T_SUB, T_PAUSED, T_REFILL, T_RET, T_NUM };
     __shared__ unsigned long long tot[T_NUM];
     // the tables first (16-byte aligned end), then the lists and the states
     Tables<R> tb = d.tb;
@@ -1978,8 +1982,9 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
     const uint32_t nt = blockDim.x, tid = threadIdx.x, nw = nt / 64;
     const int lane = lane_id();
     auto slot_of = [&](uint32_t l) { return blockIdx.x * per_block + l; };
-    if (tid < 32) (&cnt[0][0])[tid] = 0;
+    if (tid < 32) (&cnt[0][0])[tid] = (&listed[0][0])[tid] = 0;
     if (tid < T_NUM) tot[tid] = 0;
+    if (tid < 2) taken_chunks[tid] = placed[tid] = 0;
     if (tid == 0) top = 0;
     __syncthreads();
     for (uint32_t l = tid; l < per_block; l += nt) {
@@ -1994,62 +1999,59 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
     }
     // tracks of a block above a quarter more than the blocks' average wait for the next fill
     const uint32_t share = (uint32_t)((d.ctr->n_alive + d.ctr->q_base) / gridDim.x);
-    const uint32_t most = share + share / 4 + kStepsThreads;
+    const uint32_t most = share + share / 4 + 128;
     Initializer* bstack = stack + (size_t)blockIdx.x * stack_cap;
     uint32_t live0 = 0, live = 0;
-    __syncthreads();
+    uint32_t avail = 0;                      // vacancies secondaries may take this round
+    unsigned long long acc = 0;              // wave 0, lane k: slots taken from list k (vacancies: used)
     uint32_t it = 0;                         // rounds (sync: iterations) in which tracks started steps
+    __syncthreads();
     for (uint32_t round = 0;; ++round) {
-        const uint32_t* c = cnt[round & 1u];
-        uint32_t* c_next = cnt[(round + 1) & 1u];
-        // the lists' places and the chunks taken this round
-        uint32_t full = 0, underway = 0;
-        live = 0;
-        for (int k = 0; k < L_WORK; ++k) {
-            const uint32_t n = c[k];
-            live += n;
-            if (k < L_CHARGED_NEW) underway += n;
-            full += n / 64;
-        }
+        const uint32_t q = round & 1u;
+        uint32_t* c_next = cnt[q ^ 1u];
+        // The round's plan, by every wave for itself, lane k for list k: the
+        // list's place, the slots and the chunks of it taken.
+        uint32_t n = lane < L_NUM ? cnt[q][lane] : 0u;
+        const uint32_t used = round ? (placed[q ^ 1u] < avail ? placed[q ^ 1u] : avail) : 0u;
+        if (lane == L_VACANT) n -= used;
+        const int height = top < (int)stack_cap ? top : (int)stack_cap;
+        const uint32_t upto = wave_scan(n);
+        live = __builtin_amdgcn_readlane(upto, L_WORK - 1);
+        const uint32_t nv = __builtin_amdgcn_readlane(n, L_VACANT);
+        const uint32_t underway = __builtin_amdgcn_readlane(upto, L_CHARGED_NEW - 1);
         if (round == 0) live0 = live;
-        const int height = top;
-        if ((live == 0 && height == 0) || (it >= n_iter && underway == 0)) break;
+        if ((live == 0 && height == 0) || (it >= n_iter && underway == 0)) {
+            if (lane == L_VACANT) acc += used;
+            break;
+        }
         const bool start = it < n_iter && (!sync || underway == 0);
-        const bool partial = sync || !start || full < 2 * nw;
-        uint32_t first[L_WORK + 1], chunk[L_WORK + 1];
-        uint32_t n_at = 0, n_chunk = 0;
-        for (int k = 0; k < L_WORK; ++k) {
-            const uint32_t n = c[k];
-            const uint32_t take = k >= L_CHARGED_NEW && !start ? 0u : (partial ? n : n & ~63u);
-            first[k] = n_at;
-            chunk[k] = n_chunk;
-            if (tid == 0) {
-                at_list[k] = n_at;
-                c_next[k] = n - take;
-            }
-            n_at += n;
-            n_chunk += (take + 63) / 64;
+        const uint32_t full = __builtin_amdgcn_readlane(wave_scan(lane < L_WORK ? n / 64 : 0u), L_WORK - 1);
+        // (four full chunks a wave or more: the lists' ends wait.  At two, 10^4 x 1 GeV
+        // took 14.6 ms against 14.0, at one 15.9)
+        const bool partial = sync || !start || full < 4 * nw;
+        uint32_t take = lane < L_WORK ? (partial ? n : n & ~63u) : 0u;
+        if (lane >= L_CHARGED_NEW && !start) take = 0;
+        const uint32_t chunks_to = wave_scan((take + 63) / 64);
+        const uint32_t n_chunk = __builtin_amdgcn_readlane(chunks_to, L_WORK - 1);
+        const uint32_t first = upto - n, chunk = chunks_to - (take + 63) / 64;
+        acc += lane == L_VACANT ? used : take;
+        if (tid < 16) {
+            c_next[tid] = n - take;
+            listed[q ^ 1u][tid] = 0;
         }
-        first[L_WORK] = n_at;
-        chunk[L_WORK] = n_chunk;
-        const uint32_t nv = c[L_VACANT];
-        if (tid == 0) {
-            at_list[L_VACANT] = n_at;
-            c_next[L_VACANT] = nv;
-            next_chunk = 0;
-            placed = 0;
-        }
-        __syncthreads();
+        if (tid == 0) taken_chunks[q ^ 1u] = 0;
+        it += start ? 1u : 0u;
         for (uint32_t base = 0; base < per_block; base += 8 * nt)
-            list_slots(state, base + 8 * tid, per_block, lst, at_list, wbase[tid / 64]);
+            list_slots(state, base + 8 * tid, per_block, lst, first, listed[q], wbase[tid / 64]);
         __syncthreads();
+        if (tid == 0) placed[q ^ 1u] = 0;        // (read by every wave's plan above)
+        const uint32_t n_at = live;
         const uint16_t* vac = lst + n_at;
         const uint32_t room = most > live ? most - live : 0u;
-        uint32_t avail = nv < room ? nv : room;
+        avail = nv < room ? nv : room;
         // the newest records of the stack start first
-        uint32_t refill = 0;
         if (height > 0) {
-            refill = avail < (uint32_t)height ? avail : (uint32_t)height;
+            const uint32_t refill = avail < (uint32_t)height ? avail : (uint32_t)height;
             for (uint32_t i = tid; i < refill; i += nt) {
                 const uint32_t l = vac[avail - 1 - i];
                 const Initializer rec = bstack[height - 1 - (int)i];
@@ -2061,12 +2063,13 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
             __syncthreads();
             if (tid == 0) {
                 top = height - (int)refill;
-                c_next[L_VACANT] -= refill;
-                tot[T_INIT] += refill;
+                atomicSub(&c_next[L_VACANT], refill);
+                tot[T_REFILL] += refill;
             }
             avail -= refill;
             __syncthreads();
         }
+        // a track leaves its part for another list, or its slot
         auto go = [&](uint32_t l, uint8_t st) {
             state[l] = st;
             atomicAdd(&c_next[st >> 2], 1u);
@@ -2078,18 +2081,14 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         };
         for (;;) {
             uint32_t j = 0;
-            if (lane == 0) j = atomicAdd(&next_chunk, 1u);
+            if (lane == 0) j = atomicAdd(&taken_chunks[q], 1u);
             j = __builtin_amdgcn_readfirstlane(j);
             if (j >= n_chunk) break;
-            int k = 0;
-            uint32_t at = 0, end = 0;
-            for (int q = 0; q < L_WORK; ++q)
-                if (j >= chunk[q] && j < chunk[q + 1]) {
-                    k = q;
-                    at = first[q] + (j - chunk[q]) * 64;
-                    end = first[q + 1];
-                }
-            k = __builtin_amdgcn_readfirstlane(k);
+            // the last list that starts at or before chunk j
+            const int k = 63 - __clzll((long long)__ballot(lane < L_WORK && chunk <= j));
+            const uint32_t from = __builtin_amdgcn_readlane(first, k);
+            const uint32_t at = from + (j - __builtin_amdgcn_readlane(chunk, k)) * 64;
+            const uint32_t end = from + __builtin_amdgcn_readlane(take, k);
             const uint32_t i = at + (uint32_t)lane;
             const bool act = i < end;
             const uint32_t l = act ? lst[i] : 0u;
@@ -2167,18 +2166,18 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
                 count_secondaries(d, row, n_gam, n_ele, n_pos, retired != 0);
                 // secondaries: a vacant slot, the stack, or the initializer buffer
                 // (a run-time loop over the buffer's entries: one copy of the code)
-                const uint32_t at0 = sb.n > 0 ? atomicAdd(&placed, (uint32_t)sb.n) : 0u;
+                const uint32_t at0 = sb.n > 0 ? atomicAdd(&placed[q], (uint32_t)sb.n) : 0u;
 #pragma unroll 1
-                for (int q = 0; q < sb.n; ++q) {
-                    const Sec<R> v = {q == 0 ? sb.s0.T : (q == 1 ? sb.s1.T : sb.s2.T),
-                                      q == 0 ? sb.s0.ux : (q == 1 ? sb.s1.ux : sb.s2.ux),
-                                      q == 0 ? sb.s0.uy : (q == 1 ? sb.s1.uy : sb.s2.uy),
-                                      q == 0 ? sb.s0.uz : (q == 1 ? sb.s1.uz : sb.s2.uz),
-                                      q == 0 ? sb.s0.key : (q == 1 ? sb.s1.key : sb.s2.key),
-                                      q == 0 ? sb.s0.type : (q == 1 ? sb.s1.type : sb.s2.type)};
+                for (int e = 0; e < sb.n; ++e) {
+                    const Sec<R> v = {e == 0 ? sb.s0.T : (e == 1 ? sb.s1.T : sb.s2.T),
+                                      e == 0 ? sb.s0.ux : (e == 1 ? sb.s1.ux : sb.s2.ux),
+                                      e == 0 ? sb.s0.uy : (e == 1 ? sb.s1.uy : sb.s2.uy),
+                                      e == 0 ? sb.s0.uz : (e == 1 ? sb.s1.uz : sb.s2.uz),
+                                      e == 0 ? sb.s0.key : (e == 1 ? sb.s1.key : sb.s2.key),
+                                      e == 0 ? sb.s0.type : (e == 1 ? sb.s1.type : sb.s2.type)};
                     const Initializer rec = secondary_record(v, r, row, slab);
-                    if (at0 + (uint32_t)q < avail) {
-                        const uint32_t l2 = vac[at0 + (uint32_t)q];
+                    if (at0 + (uint32_t)e < avail) {
+                        const uint32_t l2 = vac[at0 + (uint32_t)e];
                         init_slot<R, true>(d, slot_of(l2), rec);
                         go(l2, ready(rec.type, false));
                         continue;
@@ -2195,20 +2194,8 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
             }
         }
         __syncthreads();
-        if (tid == 0) {
-            const uint32_t used = placed < avail ? placed : avail;
-            c_next[L_VACANT] -= used;
-            tot[T_INIT] += used;
-            if (top > (int)stack_cap) top = (int)stack_cap;
-            if (start) {
-                for (int k = L_CHARGED_NEW; k <= L_PHOTON; ++k)
-                    tot[k <= L_CHARGED ? T_CHARGED : T_PHOTON] += partial ? c[k] : c[k] & ~63u;
-            }
-            for (int p = 0; p < kNumProc; ++p) tot[T_PROC + p] += partial ? c[L_PROC0 + p] : c[L_PROC0 + p] & ~63u;
-        }
-        it += start ? 1u : 0u;
-        __syncthreads();
     }
+    __syncthreads();
     // the slots' types, and no action (the along-steps set every live track's)
     for (uint32_t l = tid; l < per_block; l += nt) {
         const uint32_t s = slot_of(l);
@@ -2216,7 +2203,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         d.type[s] = state[l] & 3;
         d.action[s] = state[l] == kVacantSlot ? A_NONE : A_IDLE;
     }
-    const uint32_t left = (uint32_t)top;
+    const uint32_t left = top < (int)stack_cap ? (uint32_t)top : stack_cap;
     if (left > 0) {
         __shared__ unsigned long long qbase;
         if (tid == 0) qbase = atomicAdd(&d.ctr->queue_size, (unsigned long long)left);
@@ -2226,13 +2213,21 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
             else atomicOr(&d.ctr->overflow, 1u);
         }
     }
-    if (tid != 0) return;
-    // live tracks at the end of the launch
-    if (live != live0) atomicAdd(&d.ctr->n_alive, (unsigned int)(live - live0));
+    if (tid >= 64) return;
+    // live tracks at the end of the launch, and the launch's counts
+    if (tid == 0 && live != live0) atomicAdd(&d.ctr->n_alive, (unsigned int)(live - live0));
     auto add = [&](int role, unsigned long long v) {
         if (v) d.part[(size_t)role * d.part_stride + blockIdx.x] += v;
     };
-    const unsigned long long n_charged = tot[T_CHARGED], n_photon = tot[T_PHOTON], n_new = n_charged - tot[T_RESUMED];
+    auto of_list = [&](int k) {
+        return (unsigned long long)__builtin_amdgcn_readlane((uint32_t)(acc >> 32), k) << 32 |
+               __builtin_amdgcn_readlane((uint32_t)acc, k);
+    };
+    const unsigned long long n_charged = of_list(L_CHARGED_NEW) + of_list(L_CHARGED);
+    const unsigned long long n_photon = of_list(L_PHOTON_NEW) + of_list(L_PHOTON), n_init = of_list(L_VACANT);
+    if (!tail && lane < kNumProc) add(W_PROC0 + lane, acc);
+    if (tid != 0) return;
+    const unsigned long long n_new = n_charged - tot[T_RESUMED];
     add(kStepsSlot + W_DRAIN, tot[T_RET]);
     if (tail) {
         add(W_DRAIN, n_charged + n_photon);
@@ -2243,8 +2238,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
     add(W_PRE, n_new + n_photon);
     if (FIELD) add(W_SUBSTEPS, n_new + tot[T_SUB]);
     add(W_PAUSED, tot[T_PAUSED]);
-    add(W_INIT, tot[T_INIT]);
-    for (int p = 0; p < kNumProc; ++p) add(W_PROC0 + p, tot[T_PROC + p]);
+    add(W_INIT, n_init + tot[T_REFILL]);
 }
 
 // ---- event completion ---------------------------------------------------------------

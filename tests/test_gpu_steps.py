@@ -80,10 +80,10 @@ def test_showers_equal_the_oracle(slots, drain):
 
 
 def test_tables_that_do_not_fit_beside_the_lists():
-    """Six materials: 70 kB of tables in FP64.  The step loops run as separate kernels that read them
+    """Sixteen materials: 185 kB of tables in FP64.  The step loops run as separate kernels that read them
     through the caches, and the drain is left out."""
     w = workloads.electron_showers_1gev_field(2)
-    w.stack.materials = [workloads.LEAD, workloads.LIQUID_ARGON] * 3
+    w.stack.materials = [workloads.LEAD, workloads.LIQUID_ARGON] * 8
     e_ref, l_ref, steps = run_oracle(w)
     s = session_for(w, n_slots=8192, graph_iterations=4, lds_tables=0, **LOCAL)
     s.set_tuning(fuse_interactions=True, drain_threshold=0xFFFFFFFF)
@@ -92,7 +92,7 @@ def test_tables_that_do_not_fit_beside_the_lists():
     edep, led = s.tallies_by_event(np.arange(w.n_events))
     s.close()
     assert c["steps"] == steps and c["work"]["drain"] == 0 and c["work"]["along_field"] > 0
-    assert_events_match(w, edep, led, e_ref, l_ref, "six materials")
+    assert_events_match(w, edep, led, e_ref, l_ref, "sixteen materials")
 
 
 def test_overflow_of_the_initializer_buffer_is_reported():
