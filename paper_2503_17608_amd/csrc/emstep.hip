@@ -716,8 +716,14 @@ void launch_steps(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool
     ln.k(R_VAC, false, true, k_vac_scatter<R>, dim3(nvs), dim3(kVacBlock), 0, st, d, 1, (uint32_t*)nullptr, n_count);
     ln.one(R_INIT, k_init<R, false>, dim3(nvb), dim3(kVacBlock), 0, st, d, 1);
     const StepsShape sh = steps_shape(n);
+    size_t lds = steps_lds(sh.per_block, d.n_tab * sizeof(R));
+    const size_t tallies = tally_bytes(d.n_rows, d.edep_stride);
+    if (lds + tallies <= kStepsLdsMax) {
+        d.tally_lds = (uint32_t)lds;
+        lds += tallies;
+    }
     ln.one(R_DRAIN, d.has_field ? k_steps<R, true> : k_steps<R, false>, dim3(sh.blocks), dim3(kStepsThreads),
-           steps_lds(sh.per_block, d.n_tab * sizeof(R)), st, d, (Initializer*)(c->ws + c->L.drain_stack),
+           lds, st, d, (Initializer*)(c->ws + c->L.drain_stack),
            c->L.stack_records / sh.blocks, sh.per_block, n_iter, sync ? 1 : 0, tail ? 1 : 0);
 }
 
