@@ -300,6 +300,12 @@ ems_status ems_poll_completed(ems_ctx* ctx, uint64_t* events, uint32_t cap, uint
  * and is read back per event, not copied every iteration). */
 ems_status ems_read_edep(ems_ctx* ctx, uint64_t event, double* per_slab, uint32_t n_slabs, ems_ledger* ledger);
 
+/* Deposits [n][n_slabs loaded] and ledgers [n] of the listed events, in that
+ * order (either output may be NULL); an unknown event is rejected and nothing
+ * is read.
+ * Paper: "Stepping algorithm" (sensitive-detector output). */
+ems_status ems_read_events(ems_ctx* ctx, const uint64_t* events, uint64_t n, double* edep, ems_ledger* ledgers);
+
 /* Read all tally rows at once: edep[max_events][n_slabs], ledgers[max_events]
  * (either may be NULL), plus the event id of every row (row_event, may be
  * NULL; unused rows hold UINT64_MAX).

@@ -219,6 +219,7 @@ struct ems_ctx {
     std::vector<RowReg> reg_pending;           // rows assigned on the host, not yet cleared on the device
     hipEvent_t staging_ev;
     bool staging_busy = false;
+    hipEvent_t read_ev[2];                     // halves of the staging buffer filled by k_read_rows
     // concurrent branches
     int n_streams = 1;
     hipStream_t workers[3] = {nullptr, nullptr, nullptr};
@@ -426,6 +427,37 @@ __global__ void k_ledger_sum(const Ledger* led, uint32_t n_rep, uint32_t ledger_
         s.n_reject_cap += l.n_reject_cap;
     }
     out[i] = s;
+}
+
+// Deposits [n][n_slabs] and ledgers [n] of the rows rows[0, n), summed over
+// their copies in copy order, into host memory the device can write: block b
+// takes row b.  (Written straight over the bus: a copy of the device's sums
+// and its completion would follow the kernel otherwise, 25 us for one event.)
+__global__ void k_read_rows(const uint32_t* rows, const double* edep, uint32_t n_rep_e, uint64_t edep_rs,
+                            uint32_t stride, uint32_t n_slabs, const Ledger* led, uint32_t n_rep, uint32_t ledger_rs,
+                            double* edep_out, Ledger* led_out)
+{
+    const uint32_t row = rows[blockIdx.x];
+    if (edep_out)
+        for (uint32_t j = threadIdx.x; j < n_slabs; j += blockDim.x) {
+            double v = 0.0;
+            for (uint32_t r = 0; r < n_rep_e; ++r) v += edep[r * edep_rs + (uint64_t)row * stride + j];
+            edep_out[(uint64_t)blockIdx.x * n_slabs + j] = v;
+        }
+    if (led_out && threadIdx.x == 0) {
+        Ledger s{};
+        for (uint32_t r = 0; r < n_rep; ++r) {
+            const Ledger& l = led[(size_t)r * ledger_rs + row];
+            s.escaped += l.escaped;
+            s.n_pair += l.n_pair;
+            s.n_annih += l.n_annih;
+            s.steps += l.steps;
+            for (int t = 0; t < 3; ++t) s.n_sec[t] += l.n_sec[t];
+            s.n_guard += l.n_guard;
+            s.n_reject_cap += l.n_reject_cap;
+        }
+        led_out[blockIdx.x] = s;
+    }
 }
 
 // Sum each row of the per-block partial counters: block w sums row w.
@@ -1059,6 +1091,8 @@ ems_status ems_create(const ems_options* opt, void* device_workspace, uint64_t b
     c->row_event.assign(opt->max_events, UINT64_MAX);
     c->row_pending.assign(opt->max_events, 0);
     c->row_gen.assign(opt->max_events, 0);
+    c->free_rows.reserve(opt->max_events);
+    c->row_of.reserve(opt->max_events);
     for (uint32_t r = opt->max_events; r > 0; --r) c->free_rows.push_back(r - 1);
     auto cleanup = [&](ems_status st) { ems_destroy(c); return st; };
     if (hipHostMalloc((void**)&c->snap, sizeof(Snapshot) * c->snap_slots, hipHostMallocDefault) != hipSuccess)
@@ -1070,6 +1104,7 @@ ems_status ems_create(const ems_options* opt, void* device_workspace, uint64_t b
     if (hipHostMalloc((void**)&c->reg_staging, sizeof(RowReg) * c->staging_cap, hipHostMallocDefault) != hipSuccess)
         return cleanup(fail(EMS_ERR_DEVICE, "hipHostMalloc registration staging"));
     (void)hipEventCreateWithFlags(&c->staging_ev, hipEventDisableTiming);
+    for (int i = 0; i < 2; ++i) (void)hipEventCreateWithFlags(&c->read_ev[i], hipEventDisableTiming);
     c->policy = opt->sort_policy;
     c->n_streams = opt->streams > 1 ? opt->streams : 1;
     for (int i = 0; i < c->n_streams - 1; ++i)
@@ -1114,6 +1149,7 @@ void ems_destroy(ems_ctx* c)
     if (c->staging) {
         (void)hipHostFree(c->staging);
         (void)hipEventDestroy(c->staging_ev);
+        for (int i = 0; i < 2; ++i) (void)hipEventDestroy(c->read_ev[i]);
         for (int i = 0; i < 3; ++i)
             if (c->workers[i]) (void)hipStreamDestroy(c->workers[i]);
         for (int p = 0; p < 2; ++p) {
@@ -1227,8 +1263,10 @@ ems_status ems_push_primaries(ems_ctx* c, const ems_primary* p, uint64_t n)
     if (n == 0) return EMS_OK;
     if (!p) return fail(EMS_ERR_INVALID_ARG, "null primaries");
     // validate everything before touching any state
+    // (the primaries of an event usually follow each other: one look-up for a run of them)
     uint64_t new_events = 0;
     std::unordered_map<uint64_t, int> seen;
+    seen.reserve(std::min<uint64_t>(n, c->free_rows.size() + 1));
     for (uint64_t i = 0; i < n; ++i) {
         const ems_primary& q = p[i];
         if (q.type < 0 || q.type > 2) return fail(EMS_ERR_INVALID_ARG, "primary type");
@@ -1239,6 +1277,7 @@ ems_status ems_push_primaries(ems_ctx* c, const ems_primary* p, uint64_t n)
         if (!(q.r[2] >= c->zp_host[q.slab] && q.r[2] <= c->zp_host[q.slab + 1]) ||
             !(std::fabs(q.r[0]) <= c->half_width && std::fabs(q.r[1]) <= c->half_width))
             return fail(EMS_ERR_INVALID_ARG, "primary position outside its slab");
+        if (i > 0 && p[i - 1].event == q.event) continue;
         if (c->row_of.find(q.event) == c->row_of.end() && seen.emplace(q.event, 1).second) ++new_events;
     }
     if (new_events > c->free_rows.size()) return fail(EMS_ERR_CAPACITY, "not enough free event rows");
@@ -1259,11 +1298,13 @@ ems_status ems_push_primaries(ems_ctx* c, const ems_primary* p, uint64_t n)
             c->staging_busy = false;
         }
         uint64_t chunk = std::min<uint64_t>(n - done, c->staging_cap);
+        uint32_t row = 0;
         for (uint64_t i = 0; i < chunk; ++i) {
             const ems_primary& q = p[done + i];
-            uint32_t row;
-            s = assign_row(c, q.event, &row);
-            if (s != EMS_OK) return s;
+            if (i == 0 || q.event != p[done + i - 1].event) {
+                s = assign_row(c, q.event, &row);
+                if (s != EMS_OK) return s;
+            }
             c->row_pending[row] += 1;
             Initializer& r = c->staging[i];
             r.T = q.T;
@@ -1462,28 +1503,74 @@ ems_status ems_poll_completed(ems_ctx* c, uint64_t* events, uint32_t cap, uint32
     return EMS_OK;
 }
 
+// Tallies of the rows rows[0, n) through the pinned staging buffer: each half
+// of it holds the row list and the results of as many rows as fit, and is
+// copied out to the caller while the other is filled.
+static ems_status read_rows(ems_ctx* c, const uint32_t* rows, uint64_t n, double* edep, ems_ledger* ledgers)
+{
+    if (c->staging_busy) {
+        HIP_TRY(hipEventSynchronize(c->staging_ev));
+        c->staging_busy = false;
+    }
+    const uint32_t ns = c->n_slabs;
+    const uint64_t half = sizeof(Initializer) * c->staging_cap / 2 / 256 * 256;
+    const uint64_t per_row = 4 + 8ull * ns + sizeof(Ledger);
+    const uint64_t fit = (half - 512) / per_row;              // (65534 slabs: four rows)
+    const uint64_t at_edep = align_up(4 * fit, 256), at_led = at_edep + 8ull * ns * fit;
+    uint64_t begin[2] = {0, 0}, count[2] = {0, 0};
+    auto collect = [&](int h) -> ems_status {
+        if (count[h] == 0) return EMS_OK;
+        HIP_TRY(hipEventSynchronize(c->read_ev[h]));
+        const char* buf = (const char*)c->staging + h * half;
+        if (edep) std::memcpy(edep + begin[h] * ns, buf + at_edep, 8ull * ns * count[h]);
+        if (ledgers) std::memcpy(ledgers + begin[h], buf + at_led, sizeof(Ledger) * count[h]);
+        count[h] = 0;
+        return EMS_OK;
+    };
+    uint64_t done = 0;
+    for (int h = 0; done < n; h ^= 1) {
+        ems_status s = collect(h);
+        if (s != EMS_OK) return s;
+        const uint64_t k = std::min(n - done, fit);
+        char* buf = (char*)c->staging + h * half;
+        std::memcpy(buf, rows + done, 4 * k);
+        hipLaunchKernelGGL(k_read_rows, dim3((uint32_t)k), dim3(128), 0, c->stream, (const uint32_t*)buf,
+                           (const double*)(c->ws + c->L.edep), c->L.n_rep_e, c->L.edep_rs, (uint32_t)c->opt.max_slabs,
+                           ns, (const Ledger*)(c->ws + c->L.ledger), c->L.n_rep, c->L.ledger_rs,
+                           edep ? (double*)(buf + at_edep) : nullptr, ledgers ? (Ledger*)(buf + at_led) : nullptr);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipEventRecord(c->read_ev[h], c->stream));
+        begin[h] = done;
+        count[h] = k;
+        done += k;
+    }
+    for (int h = 0; h < 2; ++h) {
+        ems_status s = collect(h);
+        if (s != EMS_OK) return s;
+    }
+    return EMS_OK;
+}
+
 ems_status ems_read_edep(ems_ctx* c, uint64_t event, double* per_slab, uint32_t n_slabs, ems_ledger* ledger)
 {
     if (!c) return fail(EMS_ERR_INVALID_ARG, "null context");
     auto it = c->row_of.find(event);
     if (it == c->row_of.end()) return fail(EMS_ERR_INVALID_ARG, "unknown event");
     uint32_t row = it->second;
-    if (per_slab) {
-        if (n_slabs < c->n_slabs) return fail(EMS_ERR_INVALID_ARG, "per_slab too small");
-        const uint32_t ms = (uint32_t)c->opt.max_slabs;
-        hipLaunchKernelGGL(k_edep_sum, dim3((ms + 255) / 256), dim3(256), 0, c->stream, (const double*)(c->ws + c->L.edep),
-                           c->L.n_rep_e, c->L.edep_rs, ms, row, 1u, (double*)(c->ws + c->L.edep_out));
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(per_slab, c->ws + c->L.edep_out, 8ull * c->n_slabs, hipMemcpyDeviceToHost, c->stream));
+    if (per_slab && n_slabs < c->n_slabs) return fail(EMS_ERR_INVALID_ARG, "per_slab too small");
+    return read_rows(c, &row, 1, per_slab, ledger);
+}
+
+ems_status ems_read_events(ems_ctx* c, const uint64_t* events, uint64_t n, double* edep, ems_ledger* ledgers)
+{
+    if (!c || (!events && n)) return fail(EMS_ERR_INVALID_ARG, "null");
+    std::vector<uint32_t> rows(n);
+    for (uint64_t i = 0; i < n; ++i) {
+        auto it = c->row_of.find(events[i]);
+        if (it == c->row_of.end()) return fail(EMS_ERR_INVALID_ARG, "unknown event");
+        rows[i] = it->second;
     }
-    if (ledger) {
-        hipLaunchKernelGGL(k_ledger_sum, dim3(1), dim3(64), 0, c->stream, (const Ledger*)(c->ws + c->L.ledger),
-                           c->L.n_rep, c->L.ledger_rs, row, 1u, (Ledger*)(c->ws + c->L.ledger_out));
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(ledger, c->ws + c->L.ledger_out, sizeof(Ledger), hipMemcpyDeviceToHost, c->stream));
-    }
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return EMS_OK;
+    return read_rows(c, rows.data(), n, edep, ledgers);
 }
 
 ems_status ems_read_all_tallies(ems_ctx* c, double* edep, ems_ledger* ledgers, uint64_t* row_event)
@@ -1522,6 +1609,7 @@ ems_status ems_release_events(ems_ctx* c, const uint64_t* events, uint64_t n)
     if (!c || (!events && n)) return fail(EMS_ERR_INVALID_ARG, "null");
     // validate all first: nothing is released on error
     std::unordered_map<uint64_t, int> seen;
+    seen.reserve(n);
     for (uint64_t i = 0; i < n; ++i) {
         if (c->row_of.find(events[i]) == c->row_of.end()) return fail(EMS_ERR_INVALID_ARG, "unknown event");
         if (!seen.emplace(events[i], 1).second) return fail(EMS_ERR_INVALID_ARG, "event listed twice");

@@ -104,6 +104,7 @@ _sigs = {
     "ems_poll_completed": (C.c_int, [_P, _P, C.c_uint32, C.POINTER(C.c_uint32)]),
     "ems_last_counters": (C.c_int, [_P, C.POINTER(Counters)]),
     "ems_read_edep": (C.c_int, [_P, C.c_uint64, _P, C.c_uint32, _P]),
+    "ems_read_events": (C.c_int, [_P, _P, C.c_uint64, _P, _P]),
     "ems_read_all_tallies": (C.c_int, [_P, _P, _P, _P]),
     "ems_release_event": (C.c_int, [_P, C.c_uint64]),
     "ems_release_events": (C.c_int, [_P, _P, C.c_uint64]),
@@ -269,10 +270,21 @@ class Session:
 
     def tallies_by_event(self, events):
         """edep[len(events), n_slabs] and ledgers ordered like `events`."""
-        e, led, ev = self.read_all()
-        row = {int(x): i for i, x in enumerate(ev) if x != np.uint64(2 ** 64 - 1)}
-        idx = np.array([row[int(x)] for x in events])
-        return e[idx], led[idx]
+        try:
+            if not (isinstance(events, np.ndarray) and events.dtype.kind in "iu"):
+                events = np.array([int(x) for x in events], dtype=np.uint64)
+        except OverflowError as err:
+            raise KeyError(f"an event of {events!r} is not in the session") from err
+        if events.ndim != 1:
+            raise TypeError("events must be a one-dimensional sequence of event ids")
+        ev = np.ascontiguousarray(events.astype(np.uint64, copy=False))
+        e = np.empty((len(ev), self.n_slabs))
+        led = np.empty(len(ev), dtype=LEDGER_DTYPE)
+        status = _lib.ems_read_events(self._h, _ptr(ev), len(ev), _ptr(e), _ptr(led))
+        if status == ERR_INVALID_ARG:
+            raise KeyError(f"an event of {events!r} is not in the session")
+        _check(status, "ems_read_events")
+        return e, led
 
     def release(self, event):
         """Release one event id, or an array of them (one clearing kernel)."""

@@ -105,3 +105,32 @@ def test_overflow_of_the_initializer_buffer_is_reported():
         s.run(1_000_000)
     assert e.value.status == emstep.ERR_CAPACITY
     s.close()
+
+
+@pytest.mark.parametrize("n_events,max_events,order", [(1, 1, "one"), (7, 40, "reversed"), (3000, 3000, "shuffled"),
+                                                       (40, 40, "twice")])
+def test_events_are_read_in_the_callers_order(n_events, max_events, order):
+    """Deposits and ledgers of listed events (through both halves of the staging buffer for 3000 events of 100
+    slabs, 2.5 MB) are the rows of the whole-table read, bit for bit."""
+    w = workloads.electron_showers_1gev_field(n_events)
+    w.primaries["T"] = 5.0
+    w.primaries["event"] += 5
+    s = session_for(w, n_slots=4096, max_events=max_events, n_initializers=1 << 16, **LOCAL)
+    s.set_tuning(fuse_interactions=True)
+    s.push(w.primaries)
+    s.run(100_000)
+    e_all, l_all, ev_all = s.read_all()
+    ids = np.arange(5, 5 + n_events)
+    ids = {"one": ids, "reversed": ids[::-1], "shuffled": np.random.default_rng(1).permutation(ids),
+           "twice": np.repeat(ids, 2)}[order]
+    edep, led = s.tallies_by_event(ids)
+    at = {int(x): i for i, x in enumerate(ev_all)}
+    rows = np.array([at[int(x)] for x in ids])
+    assert edep.tobytes() == e_all[rows].tobytes() and led.tobytes() == l_all[rows].tobytes()
+    one_e, one_l = s.read_edep(int(ids[0]))
+    assert one_e.tobytes() == edep[0].tobytes() and one_l.tobytes() == led[0].tobytes()
+    assert edep.sum() > 0
+    for bad in ([4], [5, 5 + n_events], [-1], np.array([-1])):
+        with pytest.raises(KeyError):
+            s.tallies_by_event(bad)
+    s.close()
