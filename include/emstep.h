@@ -68,7 +68,10 @@ typedef enum {
 
 typedef enum { EMS_FP64 = 0, EMS_MIXED = 1 } ems_precision;
 /* Track ordering before the along-step and the interaction kernels:
- *   NONE      every kernel runs over all slots and masks by next action;
+ *   NONE      no order.  With a tuning set (ems_set_tuning), every kernel runs
+ *             over all slots and masks by next action; in a context that no
+ *             tuning was set for, the library chooses the schedule (the
+ *             block-local step loops, see ems_tuning);
  *   PARTITION stable counting sort of slot indices by next action (LDS
  *             histogram, scan, stable scatter) at both sort points;
  *   RADIX     the same with the composite key action|particle|material;
@@ -392,13 +395,14 @@ ems_status ems_sort_keys_noalloc(ems_ctx* ctx, const uint8_t* keys, uint64_t n, 
  * sort policy itself (partition, radix, queue) is one per context.
  *
  * Block-local step loops: with the policy PARTITION, fuse_interactions and
- * fuse_along set, one stream, no parent-slot reuse, no deterministic appends
+ * fuse_along set, or with the policy NONE and no tuning ever set, and with
+ * no parent-slot reuse, no deterministic appends
  * and no profile of another role than vacancies, init or drain, ems_step and
  * ems_run run their iterations in launches in which every block steps the
  * tracks of its own slots (ems_step: every live track once per iteration;
  * ems_run: a block's tracks as its waves get to them), as long as the tables
- * fit the blocks' LDS.  The sort points, block sizes and graph batches then
- * play no part.  The results are those of the separate kernels.
+ * fit the blocks' LDS.  The sort points, block sizes, graph batches and worker
+ * streams then play no part.  The results are those of the separate kernels.
  *
  * Drain (ems_run only; 0 = off): once the latest counter snapshot shows fewer
  * than drain_threshold tracks alive, queued or pending, and no more than the

@@ -6,7 +6,7 @@
 //   -> [sort point 1, by the along-step action of each type]
 //   -> pre-step and along-step (neutral, charged, field; one kernel each)
 //   -> [sort point 2] -> seven interaction kernels, or one fused launch;
-// or, with the partition policy and every launch fused (local_steps), for many
+// or, where every launch is fused or no schedule is asked for (local_steps), for many
 // iterations at once,
 //   vacancy count / scatter -> initialization -> k_steps,
 // in which every block steps the tracks of its own slots; after each launch
@@ -243,6 +243,7 @@ struct ems_ctx {
     uint32_t drain_steps = kDrainStepsDefault;
     uint32_t reuse_parent = 0;        // parent-slot reuse for the first secondary
     uint32_t fuse_interactions = 0;   // one launch for the seven interaction kernels
+    bool tuned = false;               // ems_set_tuning was called: the schedule is the caller's
     uint32_t fuse_along = 1;          // one launch for the photon and field along-steps
     int block[16] = {0};
     // profiling
@@ -772,16 +773,23 @@ bool steps_fit(const ems_ctx* c)
     return steps_lds(steps_shape(c->opt.n_slots).per_block, tables) <= kStepsLdsMax;
 }
 
-// Step iterations run as block-local step loops: slots partitioned by action
-// on one stream with every launch fused.  (The other policies and unfused
-// settings ask for their own kernels, deterministic appends for a fixed
-// order, parent-slot reuse for its own placement, and a profile of the
-// kernels of an iteration for those kernels.)
+// Step iterations run as block-local step loops: where every launch is fused
+// and slots are partitioned by action, and where the caller left the schedule
+// to the library (no policy, no tuning; the tracks' results are the same
+// under every schedule).  With the default options, masked kernels on four
+// streams against the loops, a whole call: 500 electrons of 1 GeV in 2^17
+// slots 35.9 and 6.4 ms, one of 10 MeV 8.4 and 0.53, 5000 of 1 GeV in 2^20
+// slots 70.0 and 11.2, 2000 of 1 GeV in 1024 slots 1989 and 457: no size at
+// which the masked kernels are the faster ones.  (The other policies, and no policy by tuning,
+// ask for their own kernels, deterministic appends for a fixed order,
+// parent-slot reuse for its own placement, and a profile of the kernels of an
+// iteration for those kernels.)
 bool local_steps(const ems_ctx* c)
 {
     const uint32_t own = (1u << R_VAC) | (1u << R_INIT) | (1u << R_DRAIN);
-    return c->policy == EMS_SORT_PARTITION && c->fuse_interactions && c->fuse_along && c->n_streams == 1 &&
-           !c->reuse_parent && !c->opt.deterministic && !(c->prof_mask & ~own) && steps_fit(c);
+    const bool fused = c->policy == EMS_SORT_PARTITION && c->fuse_interactions && c->fuse_along;
+    const bool untuned = c->policy == EMS_SORT_NONE && !c->tuned;
+    return (fused || untuned) && !c->reuse_parent && !c->opt.deterministic && !(c->prof_mask & ~own) && steps_fit(c);
 }
 
 // Record the events whose rows emptied in the iterations launched so far.
@@ -1817,6 +1825,7 @@ ems_status ems_set_tuning(ems_ctx* c, const ems_tuning* t)
     if (c->opt.deterministic && (t->sort_policy == EMS_SORT_QUEUE || t->drain_threshold > 0))
         return fail(EMS_ERR_INVALID_ARG, "deterministic appends do not combine with the queue policy or the drain");
     c->policy = t->sort_policy;
+    c->tuned = true;
     c->tail_threshold = t->tail_threshold;
     c->phase_sort[0] = t->phase_sort[0];
     c->phase_sort[1] = t->phase_sort[1];

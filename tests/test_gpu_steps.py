@@ -134,3 +134,27 @@ def test_events_are_read_in_the_callers_order(n_events, max_events, order):
         with pytest.raises(KeyError):
             s.tallies_by_event(bad)
     s.close()
+
+
+@pytest.mark.parametrize("tuning,streams,local", [
+    (None, 4, True),                       # no schedule asked for: the library's choice
+    (dict(), 4, False),                    # any tuning: no policy means masked kernels
+    (dict(sort_policy="none", fuse_interactions=True), 1, False),
+    (dict(sort_policy="partition"), 4, False),
+    (dict(sort_policy="partition", fuse_interactions=True), 4, True),
+])
+def test_schedules_that_run_as_block_local_loops(tuning, streams, local):
+    from paper_2503_17608_amd import emstep
+    w = workloads.electron_showers_1gev_field(3)
+    e_ref, l_ref, steps = run_oracle(w)
+    s = session_for(w, n_slots=5001, n_initializers=1 << 18, sort_policy="none", graph_iterations=0, streams=streams)
+    if tuning is not None:
+        s.set_tuning(**tuning)
+    s.profile(emstep.role_mask("drain"))   # the loops' launches
+    s.push(w.primaries)
+    c = s.run(10_000_000)
+    assert (s.profile_read().get("drain", (0.0, 0))[1] > 0) == local
+    assert c["steps"] == steps and c["alive"] == 0 and c["queued"] == 0
+    edep, led = s.tallies_by_event(np.arange(3, dtype=np.uint64))
+    assert_events_match(w, edep, led, e_ref, l_ref, (tuning, streams))
+    s.close()
