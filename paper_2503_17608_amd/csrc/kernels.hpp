@@ -1937,6 +1937,17 @@ __device__ __forceinline__ void list_slots(const uint8_t* state, uint32_t l, uin
     constexpr int NW = (L_NUM + 2) / 3;
     static_assert(L_NUM <= 15, "4-bit fields of the lists (and one for no slot)");
     const uint64_t st = l < per_block ? *reinterpret_cast<const uint64_t*>(state + l) : ~0ull;
+    constexpr uint64_t kAllVacant = 0x0101010101010101ull * kVacantSlot;
+    if (__ballot(st != kAllVacant) == 0) {
+        // 512 vacant slots, as most are where a block has many more slots
+        // than tracks (16 events of up to 100 GeV in 2^22 slots: 71.2 ms
+        // counted like the others, 68.5 ms so)
+        uint32_t at = 0;
+        if (lane_id() == L_VACANT) at = first + atomicAdd(&listed[L_VACANT], 512u);
+        at = __builtin_amdgcn_readlane(at, L_VACANT) + 8 * (threadIdx.x & 63u);
+        for (int k = 0; k < 8; ++k) lst[at + k] = (uint16_t)(l + k);
+        return;
+    }
     uint64_t h = 0, rank = 0;
     for (int k = 0; k < 8; ++k) {
         const uint32_t b = (uint32_t)(st >> (8 * k)) & 0xFFu, f = b == kNoSlot ? 60u : (b >> 2) * 4;
