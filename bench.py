@@ -9,16 +9,18 @@ HBM), and `io_inclusive` times push + loop + readback of every tally.
 
 Default workload: 10^4 electrons of 1 GeV into a 50-layer Pb (2 mm) / liquid
 Ar (5 mm) stack, 40 x 40 cm, uniform 1 T field along x, 0.1 MeV cut, 2^20
-track slots, FP64, slots sorted by next action, iterations replayed from
-captured HIP graphs, the interaction kernels fused into one launch, the
-last tracks (below 65536 alive, queued or pending) stepped in block-local loops by
-the drain kernel.
+track slots, FP64, slots partitioned by next action and every launch fused,
+which the library runs as block-local step loops (one kernel, k_steps, for
+many iterations, and for the last tracks, below 65536 alive, queued or
+pending).
 
 The JSON line carries the dominant kernel's roofline: algorithmic bytes per
 launch (the kernel's units of work times the bytes per unit fixed from the
 state's field widths) divided by its average launch duration, measured with
 HIP start/stop events stamped by the kernel's own dispatch packets in one
-extra pass over the same batch (graph replay off for that pass); `traffic`
+extra pass over the same batch (k_steps, whose units are those of every
+action; where the tuning asks for the kernels of single actions, the field
+along-step's, graph replay off for that pass); `traffic`
 is the calibrated hardware byte count per launch from a committed counter
 summary, when one was taken on the current kernel sources and this
 configuration; and the oracle's throughput on the host cores for a bounded
@@ -162,7 +164,7 @@ def parse():
     ap.add_argument("--drain-threshold", type=int, default=65536,
                     help="drain the last tracks in block-local loops below this many live+queued+pending (0 = off)")
     ap.add_argument("--drain-steps", type=int, default=4096,
-                    help="drain rounds per launch (each of up to 4 steps per track)")
+                    help="most rounds of a drain launch")
     ap.add_argument("--reuse-parent-slot", type=int, default=0, help="a finished track hands its slot to a secondary")
     ap.add_argument("--fuse-interactions", type=int, default=1, help="one launch for the seven interaction kernels")
     ap.add_argument("--phase-sort", type=lambda x: int(x, 0), nargs=2, default=[0x0, 0xFFFFFFFF],
@@ -173,7 +175,7 @@ def parse():
                          "runs masked), sort point 2 always")
     ap.add_argument("--fuse-along", type=int, default=1,
                     help="one launch for the photon and field along-steps (with a field and one stream)")
-    ap.add_argument("--roofline-kernel", default="along_field")
+    ap.add_argument("--roofline-kernel", default="auto")
     ap.add_argument("--no-roofline", action="store_true")
     ap.add_argument("--cpu-events", type=int, default=10000, help="oracle sample (events); 0 = skip")
     ap.add_argument("--compare", action="store_true", help="also time the other sort policies")
@@ -274,7 +276,10 @@ def run_variant(w, args, precision, policy, init_partition, prof_kernel, tune=No
         if prof_kernel:
             # one more pass over the same batch with HIP events around the kernel
             from paper_2503_17608_amd import emstep
-            s.profile(emstep.role_mask(prof_kernel))
+            if prof_kernel == "auto":
+                prof_kernel = "steps" if step_loops(s.tuning()) else "along_field"
+            # (the launches of the block-local loops have the drain's role)
+            s.profile(emstep.role_mask("drain" if prof_kernel == "steps" else prof_kernel))
             s.profile_read()
             cp0 = s.counters()
             time_batch(s, w.primaries, events)
@@ -288,6 +293,7 @@ def run_variant(w, args, precision, policy, init_partition, prof_kernel, tune=No
     steps = c1["steps"] - c0["steps"]
     work = {k: c1["work"][k] - c0["work"][k] for k in c1["work"]}
     return {"steps": steps, "seconds": total_t, "iterations": iters, "work": work, "prof": prof,
+            "prof_kernel": prof_kernel,
             "work_prof": work_prof, "edep": edep, "ledger": led, "tuned": tuned}
 
 
@@ -312,6 +318,13 @@ def cpu_baseline(w, n_events):
             "sample": f"first {n_events} events of the workload ({steps} track-steps, {dt:.2f} s wall)",
             "single_core": {"value": steps1 / dt1, "unit": "track-steps/s",
                             "sample": f"first {n1} events ({steps1} track-steps, {dt1:.2f} s)"}}
+
+
+def step_loops(tuning):
+    """Whether a session with this tuning steps its tracks in block-local loops."""
+    from paper_2503_17608_amd import emstep
+    return (tuning["sort_policy"] == emstep.SORT_PARTITION and tuning["fuse_interactions"] and tuning["fuse_along"] and
+            not tuning["reuse_parent_slot"])
 
 
 def fused_along(args, w):
@@ -393,17 +406,20 @@ def measured_copy_gbs(mib=1024, repeats=10):
     return 2.0 * repeats * (mib << 20) / sec / 1e9
 
 
-def path_roofline(work, steps, rate, precision, n_primaries):
-    """Whole-path HBM roofline: algorithmic bytes per track-step (every step
-    kernel's units of work times its bytes per unit, summed over the batch,
-    divided by the steps) times track-steps/s, against the HBM peak.
-    Secondaries add their initializer record (the interaction writes it);
-    their initialization is counted by the fill."""
+def path_bytes(work, precision, n_primaries):
+    """Algorithmic bytes of every step kernel's units of work.  Secondaries
+    add their initializer record (the interaction writes it); their
+    initialization is counted by the fill."""
     total = sum(kernel_bytes(k, work, precision) for k in ("along_field", "along_neutral", "along_charged",
                                                            "interactions", "init", "drain"))
     secondaries = max(work.get("init", 0) + work.get("reused_slots", 0) - n_primaries, 0)
-    total += secondaries * UNIT_BYTES[precision]["secondary"]
-    b_step = total / max(steps, 1)
+    return total + secondaries * UNIT_BYTES[precision]["secondary"]
+
+
+def path_roofline(work, steps, rate, precision, n_primaries):
+    """Whole-path HBM roofline: algorithmic bytes per track-step (path_bytes
+    divided by the steps) times track-steps/s, against the HBM peak."""
+    b_step = path_bytes(work, precision, n_primaries) / max(steps, 1)
     achieved = rate * b_step / 1e9
     return {"bound": "hbm", "bytes_per_step": b_step, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS}
@@ -724,15 +740,24 @@ def main():
                                                                  "fuse_interactions", "fuse_along", "drain_threshold",
                                                                  "phase_sort")}
         out["config"]["autotuned"]["phase_choice"] = r["tuned"].get("phase_table", {}).get("choice")
-    if prof_kernel and r["prof"].get(prof_kernel, (0, 0))[1] > 0:
-        ms, launches = r["prof"][prof_kernel]
+    prof_kernel = r["prof_kernel"]
+    role = "drain" if prof_kernel == "steps" else prof_kernel
+    if prof_kernel and r["prof"].get(role, (0, 0))[1] > 0:
+        ms, launches = r["prof"][role]
         # with fuse_along the field role's launch (k_along_both) also steps
         # the photons: its bytes and tracks are both along-steps'
         both = prof_kernel == "along_field" and fused_along(args, w)
         parts = ("along_field", "along_neutral") if both else (prof_kernel,)
+        if prof_kernel == "steps":
+            # every action's tracks; the primaries' slots are filled before it
+            parts = ("along_field", "along_neutral", "along_charged", "drain")
+            total = path_bytes(r["work_prof"], precision, len(w.primaries)) - \
+                kernel_bytes("init", {"init": len(w.primaries)}, precision)
+        else:
+            total = sum(kernel_bytes(k, r["work_prof"], precision) for k in parts)
         tracks = sum(r["work_prof"][k] for k in parts)
         avg_s = ms / 1e3 / launches
-        per_launch = sum(kernel_bytes(k, r["work_prof"], precision) for k in parts) / launches
+        per_launch = total / launches
         bpt = per_launch * launches / max(tracks, 1)
         achieved = per_launch / avg_s / 1e9
         key = {"workload": w.name, "precision": precision, "n_slots": w.n_slots, "sort_policy": args.policy,
@@ -751,7 +776,7 @@ def main():
                            "tracks_per_launch": tracks / launches, "bytes_per_track": bpt,
                            "timing": "HIP start/stop events stamped by the kernel's own dispatch packet "
                                      "(hipExtLaunchKernel) on every launch of the kernel, in one extra pass over "
-                                     "the same batch (graph replay off for that pass)"}
+                                     "the same batch"}
     out["path_roofline"] = path_roofline(r["work"], r["steps"], value, precision, args.steps * len(w.primaries))
     if not args.no_roofline and args.calibrate_copy_mib == 0:
         # (counter runs leave it out: their only copies are the calibration's)
