@@ -53,7 +53,6 @@ enum : uint8_t {
     A_PROC0 = 4,       // + process index: discrete interaction
     A_ANNIH = A_PROC0 + P_ANNIH,
     A_NUM = A_PROC0 + kNumProc,
-    A_SELECT = 0x40,   // block-local step loops: an interaction whose process is yet to be chosen
     A_NONE = 0xFF      // vacant slot
 };
 
