@@ -1886,25 +1886,22 @@ constexpr uint32_t kStepsSlots = 32768;
 enum : int {
     L_PROC0 = 0,                     // + process: the interaction
     L_REST = L_PROC0 + kNumProc,     // field step: the RK4 evaluations after the first
-    L_CHARGED_NEW,                   // pre-step and step (in a field: its first RK4 evaluation), the
-    L_CHARGED,                       //   interaction length drawn first, or left from the last step
-    L_PHOTON_NEW,                    // the same for photons
-    L_PHOTON,
+    L_CHARGED,                       // pre-step and step (in a field: its first RK4 evaluation)
+    L_PHOTON,                        // the same for photons
     L_WORK,                          // lists that hold work
     L_VACANT = L_WORK,
     L_NUM
 };
 static_assert(L_NUM <= 16, "counters of a round");
 // State byte of a slot: the list it is in << 2 | the particle type.  (Tracks
-// that draw an interaction length are listed apart from those that have one
-// left: the draw is the dearest part of a pre-step, and a wave skips it only
-// if none of its tracks needs it.)
+// that draw an interaction length share a list with those that have one left.
+// Apart, a wave of the latter skips the draw's logarithm, but the two more
+// lists leave more chunks part filled and farther apart rows in a chunk:
+// 16 x 1300 x 10 GeV 197 ms apart and 191 together, 16 events of up to
+// 100 GeV 63.8 and 62.4, 10^4 x 1 GeV 13.0 and 12.7.)
 __device__ __forceinline__ uint8_t state_of(int typ, int list) { return (uint8_t)(list << 2 | typ); }
-// ready for its next step; `drawn`: with an interaction length left
-__device__ __forceinline__ uint8_t ready(int typ, bool drawn)
-{
-    return state_of(typ, (typ == kGamma ? L_PHOTON_NEW : L_CHARGED_NEW) + (drawn ? 1 : 0));
-}
+// ready for its next step
+__device__ __forceinline__ uint8_t ready(int typ) { return state_of(typ, typ == kGamma ? L_PHOTON : L_CHARGED); }
 constexpr uint8_t kVacantSlot = L_VACANT << 2 | kDead;
 constexpr uint8_t kNoSlot = 0xFF;            // a position beyond the slot array
 
@@ -2024,7 +2021,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         uint8_t st = kNoSlot;
         if (s < d.n_slots) {
             const uint8_t t = d.type[s];
-            st = t == kDead ? kVacantSlot : ready(t, !(d.nl[s] < R(0)));
+            st = t == kDead ? kVacantSlot : ready(t);
             atomicAdd(&cnt[0][st >> 2], 1u);
         }
         state[l] = st;
@@ -2050,7 +2047,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         const uint32_t upto = wave_scan(n);
         live = __builtin_amdgcn_readlane(upto, L_WORK - 1);
         const uint32_t nv = __builtin_amdgcn_readlane(n, L_VACANT);
-        const uint32_t underway = __builtin_amdgcn_readlane(upto, L_CHARGED_NEW - 1);
+        const uint32_t underway = __builtin_amdgcn_readlane(upto, L_CHARGED - 1);
         if (round == 0) live0 = live;
         if ((live == 0 && height == 0) || (it >= n_iter && underway == 0)) {
             if (lane == L_VACANT) acc += used;
@@ -2062,7 +2059,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         // took 14.6 ms against 14.0, at one 15.9)
         const bool partial = sync || !start || full < 4 * nw;
         uint32_t take = lane < L_WORK ? (partial ? n : n & ~63u) : 0u;
-        if (lane >= L_CHARGED_NEW && !start) take = 0;
+        if (lane >= L_CHARGED && !start) take = 0;
         const uint32_t chunks_to = wave_scan((take + 63) / 64);
         const uint32_t n_chunk = __builtin_amdgcn_readlane(chunks_to, L_WORK - 1);
         const uint32_t first = upto - n, chunk = chunks_to - (take + 63) / 64;
@@ -2088,7 +2085,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
                 const uint32_t l = vac[avail - 1 - i];
                 const Initializer rec = bstack[height - 1 - (int)i];
                 init_slot<R, true>(d, slot_of(l), rec);
-                const uint8_t st = ready(rec.type, false);
+                const uint8_t st = ready(rec.type);
                 state[l] = st;
                 atomicAdd(&c_next[st >> 2], 1u);
             }
@@ -2128,7 +2125,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
             const int typ = state[l] & 3;
             uint32_t row = 0, retired = 0;
             uint8_t next = A_NONE;
-            if (k == L_CHARGED_NEW || k == L_CHARGED) {
+            if (k == L_CHARGED) {
                 if (!act) continue;
                 uint32_t att = 0, paused_n = 0, pre_n = 0;
                 bool resumed = false;
@@ -2149,15 +2146,15 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
                     go(l, state_of(typ, L_REST));
                     if (resumed) atomicAdd(&tot[T_RESUMED], 1ull);
                 } else {
-                    go(l, ready(typ, true));
+                    go(l, ready(typ));
                     if (paused_n) atomicAdd(&tot[T_PAUSED], 1ull);
                 }
-            } else if (k == L_PHOTON_NEW || k == L_PHOTON) {
+            } else if (k == L_PHOTON) {
                 if (!act) continue;
                 along_straight_track<R, false, true>(d, tb, s, kGamma, row, next, retired);
                 if (retired) end_track(l, row, retired);
                 else go(l, next >= A_PROC0 && next < A_NUM ? state_of(kGamma, next - A_PROC0 + L_PROC0)
-                                                           : ready(kGamma, true));
+                                                           : ready(kGamma));
             } else if (k == L_REST) {
                 if (!FIELD || !act) continue;
                 // the first evaluation counts toward the iteration's cap
@@ -2170,7 +2167,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
                 atomicAdd(&tot[T_SUB], (unsigned long long)(att - att0));
                 if (retired) end_track(l, row, retired);
                 else if (next >= A_PROC0 && next < A_NUM) go(l, state_of(typ, next - A_PROC0 + L_PROC0));
-                else go(l, ready(typ, true));
+                else go(l, ready(typ));
                 if (paused_n) atomicAdd(&tot[T_PAUSED], 1ull);
             } else {
                 if (!act) continue;
@@ -2179,7 +2176,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
                 double r[3] = {0.0, 0.0, 0.0};
                 uint16_t slab = 0;
                 interact_track<R, true>(d, k - L_PROC0, s, typ, sb, r, row, slab, retired);
-                go(l, retired ? kVacantSlot : ready(typ, false));
+                go(l, retired ? kVacantSlot : ready(typ));
                 if (retired) atomicAdd(&tot[T_RET], (unsigned long long)retired);
                 unsigned int n_gam = 0, n_ele = 0, n_pos = 0;
                 sb.each([&](const Sec<R>& v, int) {
@@ -2203,7 +2200,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
                     if (at0 + (uint32_t)e < avail) {
                         const uint32_t l2 = vac[at0 + (uint32_t)e];
                         init_slot<R, true>(d, slot_of(l2), rec);
-                        go(l2, ready(rec.type, false));
+                        go(l2, ready(rec.type));
                         continue;
                     }
                     const int pos = atomicAdd(&top, 1);
@@ -2268,8 +2265,8 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         return (unsigned long long)__builtin_amdgcn_readlane((uint32_t)(acc >> 32), k) << 32 |
                __builtin_amdgcn_readlane((uint32_t)acc, k);
     };
-    const unsigned long long n_charged = of_list(L_CHARGED_NEW) + of_list(L_CHARGED);
-    const unsigned long long n_photon = of_list(L_PHOTON_NEW) + of_list(L_PHOTON), n_init = of_list(L_VACANT);
+    const unsigned long long n_charged = of_list(L_CHARGED);
+    const unsigned long long n_photon = of_list(L_PHOTON), n_init = of_list(L_VACANT);
     if (!tail && lane < kNumProc) add(W_PROC0 + lane, acc);
     if (tid != 0) return;
     const unsigned long long n_new = n_charged - tot[T_RESUMED];
