@@ -1018,7 +1018,7 @@ __device__ __forceinline__ uint8_t select_process(const ProcXs<R>& xs, int typ, 
 // at rest, done by the interaction launch), so no along-step creates tracks.
 // (The block-local step loops once left the choice of the process to a pass
 // of its own, with all lanes at it: it read every such track once more, and
-// made a shower's chain of rounds half as long again.  10^4 x 1 GeV 14.0 ms so,
+// put one more round into every such step.  10^4 x 1 GeV 14.0 ms so,
 // 12.8 with the choice here; one electron 3.56 and 2.99; 16 events of up to
 // 100 GeV 68.5 and 63.4; 16 x 1300 x 10 GeV 192.4 and 193.6.)
 template <class R, bool CHARGED, bool LOCAL>
@@ -1858,8 +1858,7 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact_all(Dev<R> d)
 
 // ---- block-local step loops -----------------------------------------------------
 // One launch runs several step iterations: each block owns a share of the
-// track slots (in chunks of 64, chunk c to block c mod blocks) and steps their
-// tracks by itself, so that an iteration needs no launches, no global scan of
+// track slots (a contiguous range) and steps their tracks by itself, so that an iteration needs no launches, no global scan of
 // vacancies, no sort of the slots and no trip through the initializer buffer.
 //
 // A step is cut into the parts below, and every slot has a state byte in LDS:
@@ -1867,8 +1866,8 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact_all(Dev<R> d)
 // rounds: it lists its slots by state, then its waves take chunks of 64 slots
 // that wait for the same part until the lists are done.  So every wave runs
 // one part's code with all of its lanes, where a step in one piece keeps a
-// wave busy until its slowest lane has crossed a boundary, chosen a process
-// and ended, and no wave waits for another part to end.  While there are
+// wave busy until its slowest lane has made its evaluations and its
+// interaction, and no wave waits for another part to end.  While there are
 // chunks enough for all waves, a list's last, partial chunk waits for the
 // next round to fill up.
 //
@@ -1876,6 +1875,17 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact_all(Dev<R> d)
 // with the kernels of a step iteration.  New tracks start in the block's
 // vacant slots, wait on its stack, or go to the initializer buffer, from
 // which the next fill spreads them over all blocks.
+//
+// What bounds it.  Many tracks: VALU issue takes 51-54 % of the SIMDs' cycles
+// at two waves each (the field step holds 219 VGPRs; 168, for three waves,
+// spill), 34-41 of 64 lanes active, and waves wait 43 % of their time, mostly
+// for lines of scattered rows: asking for the next chunk's lines ahead made
+// 16 x 1300 x 10 GeV slower, 193 -> 237 ms.  Few tracks: the chain of rounds, each
+// the latency of its lists, two barriers and one chunk, 9000 cycles.
+// A batch of 10^4 x 1 GeV in 2^20 slots (88.3 M steps, FP64) took 24.8 ms as
+// separate kernels and a drain, 12.7 ms so; 16 x 1300 x 10 GeV in 2^21 348 and
+// 190; 16 events of up to 100 GeV in 2^22 92.8 and 65.4; one electron 7.2 and
+// 3.0.
 constexpr int kStepsThreads = 512;
 // Most slots of a block: 96 KB of lists, so that 2^23 slots still are one
 // block per CU (16 events of up to 100 GeV in 2^22 slots: 84 ms with 8192
