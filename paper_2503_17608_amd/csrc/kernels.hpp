@@ -1876,9 +1876,9 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact_all(Dev<R> d)
 // vacant slots, wait on its stack, or go to the initializer buffer, from
 // which the next fill spreads them over all blocks.
 //
-// What bounds it.  Many tracks: VALU issue takes 51-54 % of the SIMDs' cycles
+// What bounds it.  Many tracks: VALU issue takes 58-63 % of the SIMDs' cycles
 // at two waves each (the field step holds 219 VGPRs; 168, for three waves,
-// spill), 34-41 of 64 lanes active, and waves wait 43 % of their time, mostly
+// spill), 34-38 of 64 lanes active, and waves wait 38-42 % of their time, mostly
 // for lines of scattered rows: asking for the next chunk's lines ahead made
 // 16 x 1300 x 10 GeV slower, 193 -> 237 ms.  Few tracks: the chain of rounds, each
 // the latency of its lists, two barriers and one chunk, 9000 cycles.
