@@ -1,9 +1,10 @@
-"""Block-local step loops (partition policy, every launch fused, one stream):
+"""Block-local step loops (partition policy with every launch fused, or no
+schedule asked for):
 one iteration against the per-action kernels, bit for bit, and whole showers
 against the oracle where the loops can go wrong -- slot counts that end
 inside a chunk or a block, more tracks than slots (secondaries wait on the
 blocks' stacks and in the initializer buffer), tables that do not fit beside
-the lists."""
+the lists -- and which schedules run as such loops."""
 import numpy as np
 import pytest
 
