@@ -2036,8 +2036,13 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         }
         state[l] = st;
     }
-    // tracks of a block above a quarter more than the blocks' average wait for the next fill
-    const uint32_t share = (uint32_t)((d.ctr->n_alive + d.ctr->q_base) / gridDim.x);
+    // Tracks of a block above a quarter more than the blocks' average wait for
+    // the next fill.  (The average from words that only the vacancy pass
+    // writes: all waves of a block must place by the same number, and n_alive
+    // changes while blocks of this launch end.)
+    const Counters* ctr = d.ctr;
+    const uint32_t share = (uint32_t)(((unsigned long long)ctr->alive_before + ctr->n_take_q + ctr->n_take_p +
+                                       ctr->q_base) / gridDim.x);
     const uint32_t most = share + share / 4 + 128;
     Initializer* bstack = stack + (size_t)blockIdx.x * stack_cap;
     uint32_t live0 = 0, live = 0;
