@@ -731,10 +731,26 @@ StepsShape steps_shape(uint64_t n_slots)
     return StepsShape{(uint32_t)(per * 64), (uint32_t)((chunks + per - 1) / per)};
 }
 
+// The block-local step loops keep the tables in LDS beside their lists, where
+// they fit.
+bool steps_fit(const ems_ctx* c)
+{
+    const size_t tables = (size_t)c->n_materials * kTabPerMat * kNodes * (c->opt.precision == EMS_MIXED ? 4 : 8);
+    return steps_lds(steps_shape(c->opt.n_slots).per_block, tables) <= kStepsLdsMax;
+}
+
+template <class R, bool STAGED>
+auto steps_kernel(bool field)
+{
+    return field ? k_steps<R, true, STAGED> : k_steps<R, false, STAGED>;
+}
+
 // Up to `n_iter` step iterations in one launch (counted as `n_count`
 // iterations): vacancies, fill from the initializer buffer and the pending
 // primaries, then one launch in which every block steps its share of the
-// slots.  `tail`: the drain of a run's last tracks.
+// slots.  `tail`: the drain of a run's last tracks (with the tables read
+// through the caches its steps are counted by role, like those of the separate
+// kernels that step the rest of such a context's run).
 template <class R>
 void launch_steps(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool tail)
 {
@@ -749,28 +765,22 @@ void launch_steps(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool
     ln.k(R_VAC, false, true, k_vac_scatter<R>, dim3(nvs), dim3(kVacBlock), 0, st, d, 1, (uint32_t*)nullptr, n_count);
     ln.one(R_INIT, k_init<R, false>, dim3(nvb), dim3(kVacBlock), 0, st, d, 1);
     const StepsShape sh = steps_shape(n);
-    size_t lds = steps_lds(sh.per_block, d.n_tab * sizeof(R));
+    const bool staged = steps_fit(c);
+    size_t lds = steps_lds(sh.per_block, staged ? d.n_tab * sizeof(R) : 0);
     const size_t tallies = tally_bytes(d.n_rows, d.edep_stride);
     if (lds + tallies <= kStepsLdsMax) {
         d.tally_lds = (uint32_t)lds;
         lds += tallies;
     }
-    ln.one(R_DRAIN, d.has_field ? k_steps<R, true> : k_steps<R, false>, dim3(sh.blocks), dim3(kStepsThreads),
-           lds, st, d, (Initializer*)(c->ws + c->L.drain_stack),
-           c->L.stack_records / sh.blocks, sh.per_block, n_iter, sync ? 1 : 0, tail ? 1 : 0);
+    ln.one(R_DRAIN, staged ? steps_kernel<R, true>(d.has_field) : steps_kernel<R, false>(d.has_field),
+           dim3(sh.blocks), dim3(kStepsThreads), lds, st, d, (Initializer*)(c->ws + c->L.drain_stack),
+           c->L.stack_records / sh.blocks, sh.per_block, n_iter, sync ? 1 : 0, tail && staged ? 1 : 0);
 }
 
 void launch_steps_any(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool tail)
 {
     if (c->opt.precision == EMS_MIXED) launch_steps<float>(c, n_iter, n_count, sync, tail);
     else launch_steps<double>(c, n_iter, n_count, sync, tail);
-}
-
-// The block-local step loops keep the tables in LDS beside their lists.
-bool steps_fit(const ems_ctx* c)
-{
-    const size_t tables = (size_t)c->n_materials * kTabPerMat * kNodes * (c->opt.precision == EMS_MIXED ? 4 : 8);
-    return steps_lds(steps_shape(c->opt.n_slots).per_block, tables) <= kStepsLdsMax;
 }
 
 // Step iterations run as block-local step loops: where every launch is fused
@@ -1408,8 +1418,7 @@ ems_status ems_run(ems_ctx* c, uint64_t max_iterations, ems_counters* out)
             // snapshot shows the threshold reached again; the largest
             // threshold drains every iteration from the first
             const bool below = c->drain_threshold > 0 && left < c->drain_threshold;
-            draining = steps_fit(c) &&
-                       (c->drain_threshold == UINT32_MAX || (below && (draining || left <= left_before)));
+            draining = c->drain_threshold == UINT32_MAX || (below && (draining || left <= left_before));
             if (draining) {
                 launch_steps_any(c, c->drain_steps, 1, false, true);
                 launch_completions(c);

@@ -1995,7 +1995,11 @@ constexpr size_t steps_lds(uint32_t slots, size_t tables) { return (tables + 15)
 // new steps in the first n_iter rounds, and the steps under way are then
 // ended.  `tail` counts the steps as drain work (the last tracks of a run),
 // else by role.
-template <class R, bool FIELD>
+//
+// STAGED: the tables are copied into LDS, in front of the lists; else they are
+// read through the caches (tables that do not fit, where only the drain runs
+// these loops: see steps_fit).
+template <class R, bool FIELD, bool STAGED>
 __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* stack, uint32_t stack_cap,
                                                          uint32_t per_block, uint32_t n_iter, int sync, int tail)
 {
@@ -2010,10 +2014,12 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
     __shared__ unsigned long long tot[T_NUM];
     // the tables first (16-byte aligned end), then the lists and the states
     Tables<R> tb = d.tb;
-    R* tab = (R*)ems_lds;
-    for (int i = threadIdx.x; i < d.n_tab; i += blockDim.x) tab[i] = d.tb.v[i];
-    tb.v = tab;
-    uint16_t* lst = (uint16_t*)(ems_lds + ((size_t)d.n_tab * sizeof(R) + 15) / 16 * 16);
+    if (STAGED) {
+        R* tab = (R*)ems_lds;
+        for (int i = threadIdx.x; i < d.n_tab; i += blockDim.x) tab[i] = d.tb.v[i];
+        tb.v = tab;
+    }
+    uint16_t* lst = (uint16_t*)(ems_lds + (STAGED ? ((size_t)d.n_tab * sizeof(R) + 15) / 16 * 16 : (size_t)0));
     uint8_t* state = (uint8_t*)(lst + per_block);
     // (then the block's tallies, at tally_lds)
     const uint32_t nt = blockDim.x, tid = threadIdx.x, nw = nt / 64;

@@ -8,7 +8,7 @@ import torch
 
 import workloads
 from paper_2503_17608_amd import multistream
-from tests.gpu_helpers import assert_events_match, run_oracle, session_for
+from tests.gpu_helpers import assert_events_match, assert_same_as, run_oracle, session_for
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +54,48 @@ def test_sessions_that_share_the_gpu():
     ids = range(w.n_events)
     assert_events_match(w, np.stack([edep[i] for i in ids]), np.array([led[i] for i in ids], dtype=l_ref.dtype),
                         e_ref, l_ref, "three sessions")
+
+
+def _many_materials(n_events, n_materials):
+    w = _electrons(n_events, 1000.0)
+    w.stack.materials = [workloads.LEAD, workloads.LIQUID_ARGON] * (n_materials // 2)
+    i = np.arange(w.stack.n_slabs)
+    w.stack.slab_material = ((2 * i + i % 2) % n_materials).astype(np.int32)
+    return w
+
+
+@pytest.mark.parametrize("precision,materials,slots,policy,fused,drain,field", [
+    ("f64", 16, 8192, "partition", True, 0xFFFFFFFF, True),
+    ("f64", 16, 8192, "partition", False, 2000, True),
+    ("f64", 14, 777, "queue", True, 500, True),
+    ("f64", 16, 4096, "none", False, 2000, False),
+    ("f64", 6, 1 << 23, "partition", True, 0xFFFFFFFF, True),    # the lists of 32768 slots leave less room
+    ("mixed", 32, 8192, "radix", True, 2000, True),
+])
+def test_drain_with_tables_beyond_lds(precision, materials, slots, policy, fused, drain, field):
+    """Tables that do not fit into LDS beside a block's lists: the drain reads them through the caches.  The
+    results are the oracle's (mixed precision: those of a run without a drain)."""
+    from paper_2503_17608_amd import emstep
+    w = _many_materials(12, materials)
+    if not field:
+        w.stack.B = (0.0, 0.0, 0.0)
+    s = session_for(w, n_slots=slots, n_initializers=1 << 18, precision=precision, sort_policy=policy,
+                    graph_iterations=0, streams=1, lds_tables=0)
+    s.set_tuning(fuse_interactions=fused, drain_threshold=drain)
+    s.profile(emstep.role_mask("drain"))
+    s.push(w.primaries)
+    c = s.run()
+    assert s.profile_read().get("drain", (0.0, 0))[1] > 0
+    edep, led = s.tallies_by_event(np.arange(w.n_events))
+    if precision == "f64":
+        e_ref, l_ref, steps = run_oracle(w)
+        assert_events_match(w, edep, led, e_ref, l_ref, (materials, policy))
+    else:
+        s.profile(0)
+        s.release(np.arange(w.n_events, dtype=np.uint64))
+        s.set_tuning(drain_threshold=0)
+        s.push(w.primaries)
+        steps = s.run()["steps"] - c["steps"]
+        assert_same_as(w, edep, led, *s.tallies_by_event(np.arange(w.n_events)), (materials, policy))
+    assert c["steps"] == steps and c["alive"] == 0 and c["queued"] == 0
+    s.close()
