@@ -774,7 +774,7 @@ void launch_steps(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool
     }
     ln.one(R_DRAIN, staged ? steps_kernel<R, true>(d.has_field) : steps_kernel<R, false>(d.has_field),
            dim3(sh.blocks), dim3(kStepsThreads), lds, st, d, (Initializer*)(c->ws + c->L.drain_stack),
-           c->L.stack_records / sh.blocks, sh.per_block, n_iter, sync ? 1 : 0, tail && staged ? 1 : 0);
+           c->L.stack_records / sh.blocks, sh.per_block, n_iter, sync ? 1 : 0, tail ? 1 : 0);
 }
 
 void launch_steps_any(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool tail)

@@ -1858,7 +1858,7 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact_all(Dev<R> d)
 
 // ---- block-local step loops -----------------------------------------------------
 // One launch runs several step iterations: each block owns a share of the
-// track slots (a contiguous range) and steps their tracks by itself, so that an iteration needs no launches, no global scan of
+// track slots and steps their tracks by itself, so that an iteration needs no launches, no global scan of
 // vacancies, no sort of the slots and no trip through the initializer buffer.
 //
 // A step is cut into the parts below, and every slot has a state byte in LDS:
@@ -1993,12 +1993,12 @@ constexpr size_t steps_lds(uint32_t slots, size_t tables) { return (tables + 15)
 // only in rounds with no step under way, all together, `n_iter` times: every
 // track makes one step in each of n_iter iterations.  Otherwise tracks start
 // new steps in the first n_iter rounds, and the steps under way are then
-// ended.  `tail` counts the steps as drain work (the last tracks of a run),
-// else by role.
+// ended.  `tail`: a drain (the last tracks of a run).
 //
 // STAGED: the tables are copied into LDS, in front of the lists; else they are
 // read through the caches (tables that do not fit, where only the drain runs
-// these loops: see steps_fit).
+// these loops: see steps_fit).  The steps of a drain are counted as drain work
+// if so, else by role.
 template <class R, bool FIELD, bool STAGED>
 __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* stack, uint32_t stack_cap,
                                                          uint32_t per_block, uint32_t n_iter, int sync, int tail)
@@ -2024,7 +2024,13 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
     // (then the block's tallies, at tally_lds)
     const uint32_t nt = blockDim.x, tid = threadIdx.x, nw = nt / 64;
     const int lane = lane_id();
-    auto slot_of = [&](uint32_t l) { return blockIdx.x * per_block + l; };
+    // A block's slots: a contiguous range, or in a drain every gridDim'th 64
+    // slots.  The tracks that a drain finds are where the separate kernels left
+    // them, charged ones low in the slot array and neutral ones high, so that
+    // ranges would hold very different numbers of them (radix policy, 10^4 x
+    // 1 GeV in 2^20 slots, drain below 65536: 26.8 ms with ranges, 24.6 so).
+    const uint32_t slot0 = blockIdx.x * (tail ? 64u : per_block), row_step = tail ? 64u * gridDim.x : 64u;
+    auto slot_of = [&](uint32_t l) { return slot0 + (l >> 6) * row_step + (l & 63u); };
     if (tid < 32) (&cnt[0][0])[tid] = (&listed[0][0])[tid] = 0;
     if (tid < T_NUM) tot[tid] = 0;
     if (tid < 2) taken_chunks[tid] = placed[tid] = 0;
@@ -2279,6 +2285,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
     if (tid >= 64) return;
     // live tracks at the end of the launch, and the launch's counts
     if (tid == 0 && live != live0) atomicAdd(&d.ctr->n_alive, (unsigned int)(live - live0));
+    const bool drained = STAGED && tail;
     auto add = [&](int role, unsigned long long v) {
         if (v) d.part[(size_t)role * d.part_stride + blockIdx.x] += v;
     };
@@ -2288,11 +2295,11 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
     };
     const unsigned long long n_charged = of_list(L_CHARGED);
     const unsigned long long n_photon = of_list(L_PHOTON), n_init = of_list(L_VACANT);
-    if (!tail && lane < kNumProc) add(W_PROC0 + lane, acc);
+    if (!drained && lane < kNumProc) add(W_PROC0 + lane, acc);
     if (tid != 0) return;
     const unsigned long long n_new = n_charged - tot[T_RESUMED];
     add(kStepsSlot + W_DRAIN, tot[T_RET]);
-    if (tail) {
+    if (drained) {
         add(W_DRAIN, n_charged + n_photon);
         return;
     }

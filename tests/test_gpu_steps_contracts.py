@@ -99,3 +99,22 @@ def test_drain_with_tables_beyond_lds(precision, materials, slots, policy, fused
         assert_same_as(w, edep, led, *s.tallies_by_event(np.arange(w.n_events)), (materials, policy))
     assert c["steps"] == steps and c["alive"] == 0 and c["queued"] == 0
     s.close()
+
+
+@pytest.mark.parametrize("slots", [1, 63, 65, 16385, 40007, (1 << 23) + 65])
+def test_drain_at_ragged_slot_counts(slots):
+    """A drain deals the slots out to its blocks 64 at a time: slot counts that end inside a row of blocks, inside
+    64 slots, or fill fewer blocks than there are compute units."""
+    w = _electrons(3, 1000.0 if slots > 1 else 20.0)
+    e_ref, l_ref, steps = run_oracle(w)
+    s = session_for(w, n_slots=slots, n_initializers=1 << 18, sort_policy="radix", init_partition=True, streams=1)
+    for drain in (0xFFFFFFFF, 1000):
+        s.set_tuning(fuse_interactions=True, drain_threshold=drain)
+        s.push(w.primaries)
+        c0 = s.counters()["steps"]
+        c = s.run()
+        assert c["steps"] - c0 == steps and c["alive"] == 0 and c["queued"] == 0 and c["work"]["drain"] > 0
+        edep, led = s.tallies_by_event(np.arange(w.n_events))
+        assert_events_match(w, edep, led, e_ref, l_ref, (slots, drain))
+        s.release(np.arange(w.n_events, dtype=np.uint64))
+    s.close()
