@@ -410,8 +410,11 @@ ems_status ems_sort_keys_noalloc(ems_ctx* ctx, const uint8_t* keys, uint64_t n, 
  * with few tracks: the first snapshot never starts it; 0xFFFFFFFF drains from
  * the first iteration on), each further
  * iteration fills the vacant slots and then runs one launch of the
- * block-local loops of up to drain_steps (> 0) rounds, until its blocks have
- * no tracks left (the launch counts as one iteration).  It removes the
+ * block-local loops of up to drain_steps (> 0) rounds of up to 4 steps per
+ * track, until its blocks have no tracks left (the launch counts as one
+ * iteration).  Tables that do not fit the blocks' LDS are read through the
+ * caches there, and the steps are then counted by kernel role in
+ * ems_counters.work, not as drain steps.  The drain removes the
  * per-iteration launch latency of the last, nearly empty iterations; the
  * physics is the same per-track code.
  *

@@ -134,7 +134,10 @@ constexpr int kStepsSlot = kNumWork;
 constexpr int kNumW = 2 * kNumWork;
 static_assert(W_DRAIN < kNumWork, "work counter slots");
 constexpr uint32_t kStackMax = 1u << 19;           // records of all block stacks of the block-local step loops
-constexpr uint32_t kDrainStepsDefault = 4096;      // iterations per drain launch
+constexpr uint32_t kDrainStepsDefault = 4096;      // rounds of a drain launch (as ems_tuning counts them)
+constexpr int kDrainSubsteps = 1024;               // RK4 evaluations of a drained step before a pause
+constexpr int kDrainBurst = 4;                     // steps of a track in a round of drain_steps
+constexpr int kStepRounds = 3;                     // most rounds of the loops a step takes: first evaluation, rest, interaction
 
 // Host-visible snapshot copied to pinned memory after each batch
 struct Snapshot {

@@ -761,6 +761,7 @@ void launch_steps(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool
     const uint32_t nvs = (n + kVacSpan - 1) / kVacSpan;      // vacancy blocks
     hipStream_t st = c->stream;
     d.fill_reserve = 0;
+    if (tail) d.max_substeps = kDrainSubsteps;     // (pausing does not change a result)
     ln.k(R_VAC, true, false, k_vac_count<R>, dim3(nvs), dim3(kVacBlock), 0, st, d);
     ln.k(R_VAC, false, true, k_vac_scatter<R>, dim3(nvs), dim3(kVacBlock), 0, st, d, 1, (uint32_t*)nullptr, n_count);
     ln.one(R_INIT, k_init<R, false>, dim3(nvb), dim3(kVacBlock), 0, st, d, 1);
@@ -781,6 +782,15 @@ void launch_steps_any(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, 
 {
     if (c->opt.precision == EMS_MIXED) launch_steps<float>(c, n_iter, n_count, sync, tail);
     else launch_steps<double>(c, n_iter, n_count, sync, tail);
+}
+
+// One drain launch.  drain_steps counts rounds of up to kDrainBurst steps of a
+// track, so the launch lasts as many rounds of the loops as those steps can
+// take (or until its blocks have no tracks left).
+void launch_drain(ems_ctx* c)
+{
+    const uint64_t rounds = (uint64_t)c->drain_steps * (kDrainBurst * kStepRounds);
+    launch_steps_any(c, (uint32_t)std::min<uint64_t>(rounds, UINT32_MAX), 1, false, true);
 }
 
 // Step iterations run as block-local step loops: where every launch is fused
@@ -1420,7 +1430,7 @@ ems_status ems_run(ems_ctx* c, uint64_t max_iterations, ems_counters* out)
             const bool below = c->drain_threshold > 0 && left < c->drain_threshold;
             draining = c->drain_threshold == UINT32_MAX || (below && (draining || left <= left_before));
             if (draining) {
-                launch_steps_any(c, c->drain_steps, 1, false, true);
+                launch_drain(c);
                 launch_completions(c);
                 HIP_TRY(hipGetLastError());
                 launched += 1;

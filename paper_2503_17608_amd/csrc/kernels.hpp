@@ -2083,8 +2083,9 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         const bool start = it < n_iter && (!sync || underway == 0);
         const uint32_t full = __builtin_amdgcn_readlane(wave_scan(lane < L_WORK ? n / 64 : 0u), L_WORK - 1);
         // (four full chunks a wave or more: the lists' ends wait.  At two, 10^4 x 1 GeV
-        // took 14.6 ms against 14.0, at one 15.9)
-        const bool partial = sync || !start || full < 4 * nw;
+        // took 14.6 ms against 14.0, at one 15.9; never in a drain, which promises every
+        // track its steps)
+        const bool partial = sync || tail || !start || full < 4 * nw;
         uint32_t take = lane < L_WORK ? (partial ? n : n & ~63u) : 0u;
         if (lane >= L_CHARGED && !start) take = 0;
         const uint32_t chunks_to = wave_scan((take + 63) / 64);

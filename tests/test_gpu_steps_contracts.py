@@ -118,3 +118,33 @@ def test_drain_at_ragged_slot_counts(slots):
         assert_events_match(w, edep, led, e_ref, l_ref, (slots, drain))
         s.release(np.arange(w.n_events, dtype=np.uint64))
     s.close()
+
+
+def _iterations_needed(s, w):
+    """Iterations of the separate kernels (a profile of one of them keeps the loops away) until `w` has ended."""
+    from paper_2503_17608_amd import emstep
+    s.profile(emstep.role_mask("bremsstrahlung", "interactions"))
+    s.push(w.primaries)
+    for n in range(1, 100000):
+        c = s.step(1)
+        if c["alive"] == 0 and c["queued"] == 0 and c["pending_primaries"] == 0:
+            break
+    s.profile(0)
+    s.profile_read()
+    s.release(np.arange(w.n_events, dtype=np.uint64))
+    return n
+
+
+@pytest.mark.parametrize("n,slots,drain_steps,max_substeps", [(1, 1 << 14, 1, 10), (1, 1 << 14, 3, 1), (100, 8192, 50, 10)])
+def test_a_round_of_a_drain_is_worth_an_iteration(n, slots, drain_steps, max_substeps):
+    """In a round of drain_steps every track makes up to four steps, so a drain from the first iteration on ends
+    within 1 / drain_steps as many launches as the separate kernels need iterations."""
+    w = _electrons(n, 1000.0)
+    s = session_for(w, n_slots=slots, n_initializers=1 << 18, sort_policy="radix", streams=1, max_substeps=max_substeps)
+    s.set_tuning(fuse_interactions=True)
+    limit = -(-_iterations_needed(s, w) // drain_steps)
+    s.set_tuning(drain_threshold=0xFFFFFFFF, drain_steps=drain_steps)
+    s.push(w.primaries)
+    c = s.run(limit)
+    assert c["alive"] == 0 and c["queued"] == 0
+    s.close()
