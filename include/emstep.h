@@ -169,7 +169,7 @@ typedef struct {
 } ems_ledger;
 
 typedef struct {
-    uint64_t iterations;       /* step iterations executed so far */
+    uint64_t iterations;       /* step iterations executed so far (ems_run with block-local loops: rounds asked for) */
     uint64_t alive;            /* live tracks at the start of the last iteration */
     uint64_t queued;           /* secondary initializers waiting */
     uint64_t pending_primaries;
@@ -269,7 +269,13 @@ ems_status ems_step(ems_ctx* ctx, uint32_t iterations, ems_counters* out);
 
 /* Step until no track is alive, queued or pending, or `max_iterations` is
  * reached (then returns STATE).  The host polls device counters through a
- * pinned buffer every `graph_iterations` (or 16) iterations.  Errors:
+ * pinned buffer every `graph_iterations` (or 16) iterations.
+ * With block-local step loops (see ems_tuning) it polls every 32 rounds of
+ * them, in each of which a track makes one step at most (a step with several
+ * field evaluations or an interaction takes up to three), and counts rounds
+ * as iterations, toward max_iterations as in ems_counters.iterations.  After
+ * max_iterations rounds it runs up to as many iterations as separate kernels,
+ * so that a limit that suffices for those suffices.  Errors:
  * CAPACITY if the initializer buffer overflowed.
  * Paper: "Stepping algorithm" (the host's outer loop of step iterations);
  * "Asynchronous memory management" (termination read from counters copied to

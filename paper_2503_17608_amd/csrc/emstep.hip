@@ -878,14 +878,15 @@ ems_status drop_graph(ems_ctx* c)
     return EMS_OK;
 }
 
-// launch `iters` iterations, through a captured graph when configured
-ems_status launch_batch(ems_ctx* c, int iters, bool no_init)
+// launch `iters` iterations: as one launch of the block-local step loops
+// (`local`), or as separate kernels, through a captured graph when configured
+ems_status launch_batch(ems_ctx* c, int iters, bool no_init, bool local)
 {
     bool prof = c->prof_mask != 0;
     int gi = c->opt.graph_iterations;
     const bool graph = gi > 0 && !prof && iters == gi;
     if (graph && c->stream == nullptr) return fail(EMS_ERR_INVALID_ARG, "graph capture needs a non-null stream");
-    if (!no_init && local_steps(c)) {
+    if (local) {
         // one launch for all of them: nothing to gain from a graph
         launch_steps_any(c, (uint32_t)iters, (uint32_t)iters, true, false);
         launch_completions(c);
@@ -1378,15 +1379,16 @@ ems_status ems_step(ems_ctx* c, uint32_t iterations, ems_counters* out)
     const uint32_t gi = c->opt.graph_iterations > 0 ? (uint32_t)c->opt.graph_iterations : 0;
     uint32_t done = 0;
     // (block-local loops: launches of any number of iterations)
-    const uint32_t most = local_steps(c) ? std::max(gi, kStepsPerLaunch) : 1u;
+    const bool local = local_steps(c);
+    const uint32_t most = local ? std::max(gi, kStepsPerLaunch) : 1u;
     while (gi > 0 && iterations - done >= gi) {
-        s = launch_batch(c, (int)gi, false);
+        s = launch_batch(c, (int)gi, false, local);
         if (s != EMS_OK) return s;
         done += gi;
     }
     while (done < iterations) {
         const uint32_t n = std::min(iterations - done, most);
-        s = launch_batch(c, (int)n, false);
+        s = launch_batch(c, (int)n, false, local);
         if (s != EMS_OK) return s;
         done += n;
     }
@@ -1405,7 +1407,7 @@ ems_status ems_run(ems_ctx* c, uint64_t max_iterations, ems_counters* out)
     ems_status s = check_ready(c);
     if (s != EMS_OK) return s;
     const int batch = c->opt.graph_iterations > 0 ? c->opt.graph_iterations : 16;
-    const bool local = local_steps(c);
+    bool local = local_steps(c);
     if (local && c->opt.graph_iterations > 0 && c->prof_mask == 0 && c->stream == nullptr)
         return fail(EMS_ERR_INVALID_ARG, "graph capture needs a non-null stream");
     uint64_t launched = 0;
@@ -1441,7 +1443,7 @@ ems_status ems_run(ems_ctx* c, uint64_t max_iterations, ems_counters* out)
                 HIP_TRY(hipGetLastError());
                 launched += n;
             } else {
-                s = launch_batch(c, batch, false);
+                s = launch_batch(c, batch, false, false);
                 if (s != EMS_OK) return s;
                 launched += batch;
             }
@@ -1467,7 +1469,16 @@ ems_status ems_run(ems_ctx* c, uint64_t max_iterations, ems_counters* out)
                 return fail(EMS_ERR_CAPACITY, "initializer buffer overflow: increase n_initializers");
             }
             if (done.n_alive == 0 && done.queue_size == 0 && done.prim_next == done.prim_end) finished = true;
-            else if (launched >= max_iterations && in_flight == 0) break;
+            else if (launched >= max_iterations && in_flight == 0) {
+                // The rounds of the block-local loops that `launched` counts
+                // are less than iterations: in one a track makes a step at
+                // most, and often a third of it.  A run that would have ended
+                // within max_iterations iterations ends all the same: the
+                // rest of it takes as many, as separate kernels.
+                if (!local) break;
+                local = false;
+                launched = 0;
+            }
         }
     }
     HIP_TRY(hipStreamSynchronize(c->stream));

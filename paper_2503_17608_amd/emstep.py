@@ -238,6 +238,9 @@ class Session:
         return c.as_dict() if read else None
 
     def run(self, max_iterations=1_000_000):
+        """Step until no track is left, or raise EmsError (ERR_STATE) after max_iterations iterations.  With
+        block-local step loops these, like the counter `iterations`, are rounds of at most one step of a track;
+        a limit that suffices for the separate kernels suffices for them too."""
         c = Counters()
         _check(_lib.ems_run(self._h, int(max_iterations), C.byref(c)), "ems_run")
         return c.as_dict()

@@ -148,3 +148,27 @@ def test_a_round_of_a_drain_is_worth_an_iteration(n, slots, drain_steps, max_sub
     c = s.run(limit)
     assert c["alive"] == 0 and c["queued"] == 0
     s.close()
+
+
+@pytest.mark.parametrize("n,slots,tuned", [(1, 1 << 14, True), (1, 1 << 14, False), (20, 64, True), (100, 8192, True)])
+def test_a_limit_that_suffices_for_the_separate_kernels_suffices(n, slots, tuned):
+    from paper_2503_17608_amd import emstep
+    w = _electrons(n, 1000.0)
+    e_ref, l_ref, steps = run_oracle(w)
+    s = session_for(w, n_slots=slots, n_initializers=1 << 18, **(LOCAL if tuned else {}))
+    if tuned:
+        s.set_tuning(fuse_interactions=True)
+    limit = _iterations_needed(s, w)
+    steps0 = s.counters()["steps"]
+    s.push(w.primaries)
+    with pytest.raises(emstep.EmsError) as e:
+        s.run(16)                   # far fewer than the showers are deep
+    assert e.value.status == emstep.ERR_STATE
+    s.run()
+    s.release(np.arange(w.n_events, dtype=np.uint64))
+    s.push(w.primaries)
+    c = s.run(limit)
+    assert c["steps"] - steps0 == 2 * steps and c["alive"] == 0 and c["queued"] == 0
+    edep, led = s.tallies_by_event(np.arange(w.n_events))
+    s.close()
+    assert_events_match(w, edep, led, e_ref, l_ref, (n, slots, tuned))
