@@ -1408,8 +1408,6 @@ ems_status ems_run(ems_ctx* c, uint64_t max_iterations, ems_counters* out)
     if (s != EMS_OK) return s;
     const int batch = c->opt.graph_iterations > 0 ? c->opt.graph_iterations : 16;
     bool local = local_steps(c);
-    if (local && c->opt.graph_iterations > 0 && c->prof_mask == 0 && c->stream == nullptr)
-        return fail(EMS_ERR_INVALID_ARG, "graph capture needs a non-null stream");
     uint64_t launched = 0;
     uint64_t seq = 0;
     // batches in flight: after launching batch g we wait for the snapshot of batch g-1
@@ -1437,6 +1435,9 @@ ems_status ems_run(ems_ctx* c, uint64_t max_iterations, ems_counters* out)
                 HIP_TRY(hipGetLastError());
                 launched += 1;
             } else if (local) {
+                // (no capture here, but refused like the graph batches it stands for)
+                if (c->opt.graph_iterations > 0 && c->prof_mask == 0 && c->stream == nullptr)
+                    return fail(EMS_ERR_INVALID_ARG, "graph capture needs a non-null stream");
                 const uint32_t n = (uint32_t)std::min<uint64_t>(kStepsPerLaunch, max_iterations - launched);
                 launch_steps_any(c, n, n, false, false);
                 launch_completions(c);

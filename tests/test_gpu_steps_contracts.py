@@ -172,3 +172,23 @@ def test_a_limit_that_suffices_for_the_separate_kernels_suffices(n, slots, tuned
     edep, led = s.tallies_by_event(np.arange(w.n_events))
     s.close()
     assert_events_match(w, edep, led, e_ref, l_ref, (n, slots, tuned))
+
+
+def test_null_stream_with_graph_batches():
+    """Graph batches need a stream of their own; a run that is drained from its first iteration has none."""
+    from paper_2503_17608_amd import emstep
+    w = _electrons(3, 1000.0)
+    e_ref, l_ref, steps = run_oracle(w)
+    s = session_for(w, n_slots=4096, graph_iterations=8, stream=torch.cuda.default_stream(), **LOCAL)
+    assert s.stream.cuda_stream == 0
+    s.set_tuning(fuse_interactions=True)
+    s.push(w.primaries)
+    with pytest.raises(emstep.EmsError) as e:
+        s.run()
+    assert e.value.status == emstep.ERR_INVALID_ARG
+    s.set_tuning(drain_threshold=0xFFFFFFFF)
+    c = s.run()
+    assert c["steps"] == steps and c["alive"] == 0
+    edep, led = s.tallies_by_event(np.arange(w.n_events))
+    s.close()
+    assert_events_match(w, edep, led, e_ref, l_ref, "null stream")
