@@ -170,7 +170,8 @@ typedef struct {
 
 typedef struct {
     uint64_t iterations;       /* step iterations executed so far (ems_run with block-local loops: rounds asked for) */
-    uint64_t alive;            /* live tracks at the start of the last iteration */
+    uint64_t alive;            /* live tracks at the start of the last iteration (ems_run with block-local loops: at
+                                  the end of the last launch) */
     uint64_t queued;           /* secondary initializers waiting */
     uint64_t pending_primaries;
     uint64_t steps;            /* completed steps of tracks that have finished */

@@ -101,7 +101,8 @@ struct Counters {
     unsigned long long prim_end;       // end of pushed primaries
     unsigned long long iterations;
     unsigned int n_vac;                // vacancies found this iteration
-    unsigned int n_alive;              // live tracks at the start of this iteration
+    unsigned int n_alive;              // live tracks at the start of this iteration (after a launch of
+                                       // asynchronous block-local loops: at its end)
     unsigned int overflow;
     unsigned int n_take_q;             // initializers taken from the queue this iteration
     unsigned int n_take_p;             // primaries taken this iteration

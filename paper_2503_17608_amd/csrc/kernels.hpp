@@ -2057,7 +2057,7 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
                                        ctr->q_base) / gridDim.x);
     const uint32_t most = share + share / 4 + 128;
     Initializer* bstack = stack + (size_t)blockIdx.x * stack_cap;
-    uint32_t live0 = 0, live = 0;
+    uint32_t live0 = 0, live = 0, live_at_start = 0;
     uint32_t avail = 0;                      // vacancies secondaries may take this round
     unsigned long long acc = 0;              // wave 0, lane k: slots taken from list k (vacancies: used)
     uint32_t it = 0;                         // rounds (sync: iterations) in which tracks started steps
@@ -2107,8 +2107,9 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         const uint32_t room = most > live ? most - live : 0u;
         avail = nv < room ? nv : room;
         // the newest records of the stack start first
+        const uint32_t refill = avail < (uint32_t)height ? avail : (uint32_t)height;
+        if (start) live_at_start = live + refill;
         if (height > 0) {
-            const uint32_t refill = avail < (uint32_t)height ? avail : (uint32_t)height;
             for (uint32_t i = tid; i < refill; i += nt) {
                 const uint32_t l = vac[avail - 1 - i];
                 const Initializer rec = bstack[height - 1 - (int)i];
@@ -2284,8 +2285,10 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         }
     }
     if (tid >= 64) return;
-    // live tracks at the end of the launch, and the launch's counts
-    if (tid == 0 && live != live0) atomicAdd(&d.ctr->n_alive, (unsigned int)(live - live0));
+    // live tracks at the end of the launch (sync: at the start of its last
+    // iteration, as the separate kernels count them), and the launch's counts
+    const uint32_t counted = sync && it >= n_iter ? live_at_start : live;
+    if (tid == 0 && counted != live0) atomicAdd(&d.ctr->n_alive, (unsigned int)(counted - live0));
     const bool drained = STAGED && tail;
     auto add = [&](int role, unsigned long long v) {
         if (v) d.part[(size_t)role * d.part_stride + blockIdx.x] += v;

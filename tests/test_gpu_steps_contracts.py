@@ -192,3 +192,38 @@ def test_null_stream_with_graph_batches():
     edep, led = s.tallies_by_event(np.arange(w.n_events))
     s.close()
     assert_events_match(w, edep, led, e_ref, l_ref, "null stream")
+
+
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_live_tracks_are_counted_at_the_start_of_the_last_iteration(precision):
+    from paper_2503_17608_amd import emstep
+    w = _electrons(6, 500.0)
+    seen = []
+    for local in (True, False):
+        s = session_for(w, n_slots=1 << 16, precision=precision, **LOCAL)
+        s.set_tuning(fuse_interactions=True)
+        if not local:
+            s.profile(emstep.role_mask("interactions"))
+        s.push(w.primaries)
+        seen.append([s.step(n)["alive"] for n in (1, 1, 1, 5, 8, 1, 33, 2, 64, 16, 16, 1, 1, 40, 100, 1)])
+        s.close()
+    assert seen[0] == seen[1] and max(seen[0]) > 100 and seen[0][0] == 6 and seen[0][-1] == 0
+
+
+@pytest.mark.parametrize("slots", [1, 3, 64])
+def test_stepping_by_the_counters_ends_with_the_last_track(slots):
+    """A caller that steps until nothing is alive, queued or pending has stepped everything, also where tracks
+    wait for a slot."""
+    w = _electrons(2, 60.0)
+    e_ref, l_ref, steps = run_oracle(w)
+    for n in (1, 3):
+        s = session_for(w, n_slots=slots, n_initializers=1 << 14, streams=1)
+        s.push(w.primaries)
+        for _ in range(100000):
+            c = s.step(n)
+            if c["alive"] == 0 and c["queued"] == 0 and c["pending_primaries"] == 0:
+                break
+        assert c["steps"] == steps
+        edep, led = s.tallies_by_event(np.arange(w.n_events))
+        s.close()
+        assert_events_match(w, edep, led, e_ref, l_ref, (slots, n))
