@@ -1603,11 +1603,12 @@ ems_status ems_read_edep(ems_ctx* c, uint64_t event, double* per_slab, uint32_t 
 ems_status ems_read_events(ems_ctx* c, const uint64_t* events, uint64_t n, double* edep, ems_ledger* ledgers)
 {
     if (!c || (!events && n)) return fail(EMS_ERR_INVALID_ARG, "null");
-    std::vector<uint32_t> rows(n);
+    std::vector<uint32_t> rows;
+    rows.reserve(std::min<uint64_t>(n, c->row_of.size()));
     for (uint64_t i = 0; i < n; ++i) {
         auto it = c->row_of.find(events[i]);
         if (it == c->row_of.end()) return fail(EMS_ERR_INVALID_ARG, "unknown event");
-        rows[i] = it->second;
+        rows.push_back(it->second);
     }
     return read_rows(c, rows.data(), n, edep, ledgers);
 }
@@ -1648,7 +1649,7 @@ ems_status ems_release_events(ems_ctx* c, const uint64_t* events, uint64_t n)
     if (!c || (!events && n)) return fail(EMS_ERR_INVALID_ARG, "null");
     // validate all first: nothing is released on error
     std::unordered_map<uint64_t, int> seen;
-    seen.reserve(n);
+    seen.reserve(std::min<uint64_t>(n, c->row_of.size()));
     for (uint64_t i = 0; i < n; ++i) {
         if (c->row_of.find(events[i]) == c->row_of.end()) return fail(EMS_ERR_INVALID_ARG, "unknown event");
         if (!seen.emplace(events[i], 1).second) return fail(EMS_ERR_INVALID_ARG, "event listed twice");

@@ -227,3 +227,18 @@ def test_stepping_by_the_counters_ends_with_the_last_track(slots):
         edep, led = s.tallies_by_event(np.arange(w.n_events))
         s.close()
         assert_events_match(w, edep, led, e_ref, l_ref, (slots, n))
+
+
+def test_unknown_event_of_a_list_that_is_too_long():
+    """An unknown event is refused when it is met, whatever length the list is said to have."""
+    from paper_2503_17608_amd import emstep
+    w = _electrons(2, 20.0)
+    s = session_for(w, n_slots=1024, **LOCAL)
+    s.push(w.primaries)
+    s.run()
+    ids = np.array([0, 77], dtype=np.uint64)
+    for n in (2, 1 << 40, (1 << 64) - 1):
+        assert emstep._lib.ems_release_events(s._h, emstep._ptr(ids), n) == emstep.ERR_INVALID_ARG
+        assert emstep._lib.ems_read_events(s._h, emstep._ptr(ids), n, None, None) == emstep.ERR_INVALID_ARG
+    s.release(np.arange(2, dtype=np.uint64))
+    s.close()
