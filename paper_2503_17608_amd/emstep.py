@@ -273,18 +273,19 @@ class Session:
 
     def tallies_by_event(self, events):
         """edep[len(events), n_slabs] and ledgers ordered like `events`."""
-        try:
-            if not (isinstance(events, np.ndarray) and events.dtype.kind in "iu"):
-                events = np.array([int(x) for x in events], dtype=np.uint64)
-        except OverflowError as err:
-            raise KeyError(f"an event of {events!r} is not in the session") from err
-        if events.ndim != 1:
-            raise TypeError("events must be a one-dimensional sequence of event ids")
-        ev = np.ascontiguousarray(events.astype(np.uint64, copy=False))
+        if isinstance(events, np.ndarray) and events.ndim == 1 and events.dtype.kind in "iu":
+            if events.dtype.kind == "i" and np.any(events < 0):      # (would wrap to another event's id)
+                raise KeyError(f"an event of {events!r} is not in the session")
+            ev = np.ascontiguousarray(events.astype(np.uint64, copy=False))
+        else:
+            try:
+                ev = np.array([int(x) for x in events], dtype=np.uint64)
+            except OverflowError as err:
+                raise KeyError(f"an event of {events!r} is not in the session") from err
         e = np.empty((len(ev), self.n_slabs))
         led = np.empty(len(ev), dtype=LEDGER_DTYPE)
         status = _lib.ems_read_events(self._h, _ptr(ev), len(ev), _ptr(e), _ptr(led))
-        if status == ERR_INVALID_ARG:
+        if status == ERR_INVALID_ARG and self._h:
             raise KeyError(f"an event of {events!r} is not in the session")
         _check(status, "ems_read_events")
         return e, led
