@@ -135,6 +135,7 @@ constexpr int kStepsSlot = kNumWork;
 constexpr int kNumW = 2 * kNumWork;
 static_assert(W_DRAIN < kNumWork, "work counter slots");
 constexpr uint32_t kStackMax = 1u << 19;           // records of all block stacks of the block-local step loops
+constexpr uint64_t kQueueExtraMax = 1ull << 20;    // records of the initializer buffer beyond ems_options.n_initializers
 constexpr uint32_t kDrainStepsDefault = 4096;      // rounds of a drain launch (as ems_tuning counts them)
 constexpr int kDrainSubsteps = 1024;               // RK4 evaluations of a drained step before a pause
 constexpr int kDrainBurst = 4;                     // steps of a track in a round of drain_steps

@@ -81,6 +81,7 @@ struct Layout {
     uint64_t along_list;                   // occupied slots before the fill (masked one-launch along-steps)
     uint32_t part_stride;
     uint32_t stack_records;   // records of all block stacks of the block-local step loops
+    uint64_t queue_cap;       // records of the initializer buffer
     uint64_t total;
     uint32_t n_tiles;
 };
@@ -109,7 +110,16 @@ Layout make_layout(const ems_options& o)
     L.sphys = take(8 * n);
     L.sdone = take(8 * n);
     L.htry = take(8 * n);
-    L.queue = take(sizeof(Initializer) * o.n_initializers);
+    // The block-local loops let more tracks wait than the separate kernels do
+    // (a block takes its own newest first, whatever waits elsewhere, and hands
+    // its stack over at the end of a launch), so the buffer holds more than
+    // was asked for wherever they may run: up to 8 records per slot.  Most
+    // waiting at a time, separate kernels and loops, default options: 200 x
+    // 1 GeV in 2^14 slots 11 336 and 21 711, 8 x 100 GeV in 4096 19 483 and
+    // 33 485, 1000 x 10 GeV in 2^17 491 300 and 1 302 181 (6.2 per slot more),
+    // 2000 x 10 GeV in 2^20 1 330 695 and 1 841 563.
+    L.queue_cap = o.n_initializers + (o.deterministic ? 0ull : std::min<uint64_t>(kQueueExtraMax, 8 * n));
+    L.queue = take(sizeof(Initializer) * L.queue_cap);
     L.prims = take(sizeof(Initializer) * o.n_primaries);
     L.vac = take(4 * n);
     uint64_t nvb = (n + kVacBlock - 1) / kVacBlock;
@@ -159,7 +169,7 @@ Layout make_layout(const ems_options& o)
     L.part = take(8ull * kNumW * L.part_stride);
     L.rowsum = take(8ull * kNumW);
     L.incr = take(8ull * o.max_materials * 2 * (kNodes - 1));
-    L.stack_records = (uint32_t)std::min<uint64_t>(kStackMax, 8 * align_up(n, 256));
+    L.stack_records = (uint32_t)std::min<uint64_t>(kStackMax, 16 * align_up(n, 256));
     L.drain_stack = take(sizeof(Initializer) * (uint64_t)L.stack_records);
     L.regs = take(sizeof(RowReg) * kStagingCap);
     L.ledger_out = take(sizeof(Ledger) * (uint64_t)o.max_events);
@@ -287,7 +297,7 @@ Dev<R> make_dev(const ems_ctx* c)
     d.htry = (double*)(b + L.htry);
     d.n_slots = (uint32_t)c->opt.n_slots;
     d.queue = (Initializer*)(b + L.queue);
-    d.queue_cap = c->opt.n_initializers;
+    d.queue_cap = c->L.queue_cap;
     d.prims = (Initializer*)(b + L.prims);
     d.prim_cap = c->opt.n_primaries;
     d.vac = (uint32_t*)(b + L.vac);
@@ -1739,7 +1749,7 @@ ems_status ems_debug_read_secondaries(ems_ctx* c, ems_track* out, uint64_t cap, 
     Snapshot sn;
     ems_status s = snapshot_now(c, &sn);
     if (s != EMS_OK) return s;
-    uint64_t q = sn.queue_size < c->opt.n_initializers ? sn.queue_size : c->opt.n_initializers;
+    uint64_t q = std::min<uint64_t>(sn.queue_size, c->L.queue_cap);
     *n = q;
     uint64_t m = q < cap ? q : cap;
     if (m == 0 || !out) return EMS_OK;

@@ -268,3 +268,39 @@ def test_event_lists_of_every_kind():
     s.close()
     with pytest.raises(emstep.EmsError):
         s.tallies_by_event([7])
+
+
+@pytest.mark.parametrize("n,energy,slots,tuning", [
+    (20, 1000.0, 1 << 14, dict(sort_policy="partition", fuse_interactions=True)),
+    (200, 1000.0, 1024, dict(sort_policy="partition", fuse_interactions=True)),
+    (200, 1000.0, 1 << 14, None),
+    (8, 100000.0, 4096, None),
+    (1, 100000.0, 4096, dict(sort_policy="radix", fuse_interactions=True, drain_threshold=0xFFFFFFFF)),
+    (8, 100000.0, 4096, dict(sort_policy="radix", fuse_interactions=True, drain_threshold=0xFFFFFFFF)),
+])
+def test_a_buffer_that_suffices_for_the_separate_kernels_suffices(n, energy, slots, tuning):
+    """The initializer buffer as large as the most secondaries that wait while separate kernels run (a drain: a
+    tenth of it, which its own stacks make up for)."""
+    from paper_2503_17608_amd import emstep
+    w = _electrons(n, energy)
+    streams = 1 if tuning else 4
+    s = session_for(w, n_slots=slots, streams=streams, init_partition=tuning is not None)
+    s.set_tuning(**{k: v for k, v in (tuning or {}).items() if k != "drain_threshold"})
+    s.profile(emstep.role_mask("bremsstrahlung", "interactions"))
+    s.push(w.primaries)
+    most = 0
+    while True:
+        c = s.step(1)
+        most = max(most, c["queued"])
+        if c["alive"] == 0 and c["queued"] == 0 and c["pending_primaries"] == 0:
+            break
+    e_ref, l_ref = s.tallies_by_event(np.arange(w.n_events))
+    s.close()
+    s = session_for(w, n_slots=slots, streams=streams, init_partition=tuning is not None,
+                    n_initializers=max(1, most // 10 if tuning and "drain_threshold" in tuning else most))
+    if tuning:
+        s.set_tuning(**tuning)
+    s.push(w.primaries)
+    assert s.run()["steps"] == c["steps"]
+    assert_same_as(w, *s.tallies_by_event(np.arange(w.n_events)), e_ref, l_ref, (n, energy, slots))
+    s.close()
