@@ -403,7 +403,8 @@ ems_status ems_sort_keys_noalloc(ems_ctx* ctx, const uint8_t* keys, uint64_t n, 
  * sort policy itself (partition, radix, queue) is one per context.
  *
  * Block-local step loops: with the policy PARTITION, fuse_interactions and
- * fuse_along set, or with the policy NONE and no tuning ever set, and with
+ * fuse_along set, or with the policy NONE and no tuning set (since
+ * ems_create or ems_clear_tuning), and with
  * no parent-slot reuse, no deterministic appends
  * and no profile of another role than vacancies, init or drain, ems_step and
  * ems_run run their iterations in launches in which every block steps the
@@ -465,6 +466,13 @@ typedef struct {
 } ems_tuning;
 ems_status ems_set_tuning(ems_ctx* ctx, const ems_tuning* t);
 ems_status ems_get_tuning(ems_ctx* ctx, ems_tuning* t);
+
+/* Back to the tuning of a new context: the sort policy of ems_options, every
+ * knob at its default, and with the policy NONE the schedule left to the
+ * library again (a tuning, also one that changes nothing, asks for masked
+ * kernels there).
+ * Paper: as ems_set_tuning. */
+ems_status ems_clear_tuning(ems_ctx* ctx);
 
 /* Average duration [ms] of each kernel over the iterations launched since the
  * last call, measured with HIP events around every launch on the library's

@@ -253,7 +253,7 @@ struct ems_ctx {
     uint32_t drain_steps = kDrainStepsDefault;
     uint32_t reuse_parent = 0;        // parent-slot reuse for the first secondary
     uint32_t fuse_interactions = 0;   // one launch for the seven interaction kernels
-    bool tuned = false;               // ems_set_tuning was called: the schedule is the caller's
+    bool tuned = false;               // the schedule is the caller's (ems_set_tuning, until ems_clear_tuning)
     uint32_t fuse_along = 1;          // one launch for the photon and field along-steps
     int block[16] = {0};
     // profiling
@@ -1877,6 +1877,22 @@ ems_status ems_set_tuning(ems_ctx* c, const ems_tuning* t)
     c->fuse_interactions = t->fuse_interactions ? 1u : 0u;
     c->fuse_along = t->fuse_along ? 1u : 0u;
     for (int i = 0; i < 16; ++i) c->block[i] = t->block[i];
+    return drop_graph(c);
+}
+
+ems_status ems_clear_tuning(ems_ctx* c)
+{
+    if (!c) return fail(EMS_ERR_INVALID_ARG, "null");
+    c->policy = c->opt.sort_policy;
+    c->tuned = false;
+    c->tail_threshold = 0;
+    c->phase_sort[0] = c->phase_sort[1] = 0xFFFFFFFFu;
+    c->drain_threshold = 0;
+    c->drain_steps = kDrainStepsDefault;
+    c->reuse_parent = 0;
+    c->fuse_interactions = 0;
+    c->fuse_along = 1;
+    for (int i = 0; i < 16; ++i) c->block[i] = 0;
     return drop_graph(c);
 }
 

@@ -117,6 +117,7 @@ _sigs = {
     "ems_sort_keys_noalloc": (C.c_int, [_P, _P, C.c_uint64, C.c_int32, _P]),
     "ems_set_tuning": (C.c_int, [_P, C.POINTER(Tuning)]),
     "ems_get_tuning": (C.c_int, [_P, C.POINTER(Tuning)]),
+    "ems_clear_tuning": (C.c_int, [_P]),
     "ems_profile_enable": (C.c_int, [_P, C.c_int32]),
     "ems_profile_read": (C.c_int, [_P, _P, _P, _P, C.c_uint32, C.POINTER(C.c_uint32)]),
 }
@@ -365,7 +366,8 @@ class Session:
         """Change knobs that affect speed only; block maps kernel role names to
         block sizes; phase_sort is a pair of 32-bit masks over occupancy
         buckets floor(log2 live tracks): bit b of mask p set = sort point p
-        reorders in iterations of bucket b."""
+        reorders in iterations of bucket b.  With the policy "none" any call, also one that changes nothing, asks
+        for masked kernels, until clear_tuning."""
         cur = Tuning()
         _check(_lib.ems_get_tuning(self._h, C.byref(cur)), "ems_get_tuning")
         if sort_policy is not None:
@@ -389,6 +391,10 @@ class Session:
             cur.phase_sort[0] = int(phase_sort[0]) & 0xFFFFFFFF
             cur.phase_sort[1] = int(phase_sort[1]) & 0xFFFFFFFF
         _check(_lib.ems_set_tuning(self._h, C.byref(cur)), "ems_set_tuning")
+
+    def clear_tuning(self):
+        """Back to a new session's tuning: with the policy "none" the library chooses the schedule again."""
+        _check(_lib.ems_clear_tuning(self._h), "ems_clear_tuning")
 
     def profile(self, mask):
         _check(_lib.ems_profile_enable(self._h, int(mask)), "ems_profile_enable")

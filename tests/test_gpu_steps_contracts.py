@@ -304,3 +304,26 @@ def test_a_buffer_that_suffices_for_the_separate_kernels_suffices(n, energy, slo
     assert s.run()["steps"] == c["steps"]
     assert_same_as(w, *s.tallies_by_event(np.arange(w.n_events)), e_ref, l_ref, (n, energy, slots))
     s.close()
+
+
+def test_a_cleared_tuning_leaves_the_schedule_to_the_library():
+    from paper_2503_17608_amd import emstep
+    w = _electrons(2, 200.0)
+    s = session_for(w, n_slots=4096)
+    new = s.tuning()
+
+    def loops():
+        s.profile(emstep.role_mask("drain"))
+        s.push(w.primaries)
+        s.run()
+        n = s.profile_read().get("drain", (0.0, 0))[1]
+        s.profile(0)
+        s.release(np.arange(2, dtype=np.uint64))
+        return n > 0
+
+    assert loops()
+    s.set_tuning(block={"compton": 128}, tail_threshold=5, phase_sort=(0, 1), fuse_along=False)
+    assert not loops()
+    s.clear_tuning()
+    assert s.tuning() == new and loops()
+    s.close()
