@@ -21,7 +21,12 @@ occupancy masked stepping and no drain look best):
    iteration whatever the launch shape), so each bucket keeps the
    combination whose iterations in that bucket took the least GPU time;
 5. fused or per-process interaction kernels, and the drain threshold below
-   which the last tracks are drained in block-local loops, timed end to end.
+   which the last tracks are drained in block-local loops, timed end to end;
+6. the block-local step loops (partition with every launch fused: no
+   combination of the steps above need have come to it) with each drain
+   threshold, timed end to end against the best of the above.  They take no
+   part of the block sizes, the tail threshold or the phase table, which are
+   kept for the runs that use separate kernels all the same.
 
 Results can be cached in a JSON file keyed by a workload signature.
 """
@@ -226,6 +231,19 @@ def autotune(session, sample, policies=("none", "partition", "radix", "queue"),
         drain_t[dth] = min(_run(session, sample, events) for _ in range(repeats))
     best_drain = min(drain_t, key=drain_t.get)
     say("fuse", fuse_t, "fuse along", along_t, "drain", drain_t)
+    # 6. the block-local step loops
+    loops_t = {}
+    if "partition" in policies:
+        for dth in drains:
+            session.set_tuning(sort_policy="partition", fuse_interactions=True, fuse_along=True, drain_threshold=dth)
+            loops_t[dth] = min(_run(session, sample, events) for _ in range(repeats))
+        say("block-local step loops", loops_t)
+    if loops_t and min(loops_t.values()) < min(drain_t.values()):
+        best_policy, best_fuse, best_along = "partition", True, True
+        best_drain = min(loops_t, key=loops_t.get)
+        if phases and not phase_info:
+            session.set_tuning(drain_threshold=0)
+            phase_masks, phase_info = phase_table(session, sample, events)
     session.set_tuning(sort_policy=best_policy, tail_threshold=best_th, block=best_block,
                        fuse_interactions=best_fuse, fuse_along=best_along, drain_threshold=best_drain,
                        phase_sort=phase_masks)
@@ -236,6 +254,7 @@ def autotune(session, sample, policies=("none", "partition", "radix", "queue"),
               "fuse_seconds": {str(k): v for k, v in fuse_t.items()},
               "fuse_along_seconds": {str(k): v for k, v in along_t.items()},
               "drain_seconds": {str(k): v for k, v in drain_t.items()},
+              "loops_seconds": {str(k): v for k, v in loops_t.items()},
               "block_ms": {r: {str(b): v for b, v in d.items()} for r, d in per_role.items()}}
     if cache and key:
         db = json.load(open(cache)) if os.path.exists(cache) else {}
