@@ -749,6 +749,25 @@ bool steps_fit(const ems_ctx* c)
     return steps_lds(steps_shape(c->opt.n_slots).per_block, tables) <= kStepsLdsMax;
 }
 
+// Step iterations run as block-local step loops: where every launch is fused
+// and slots are partitioned by action, and where the caller left the schedule
+// to the library (no policy, no tuning; the tracks' results are the same
+// under every schedule).  With the default options, masked kernels on four
+// streams against the loops, a whole call: 500 electrons of 1 GeV in 2^17
+// slots 35.9 and 6.4 ms, one of 10 MeV 8.4 and 0.53, 5000 of 1 GeV in 2^20
+// slots 70.0 and 11.2, 2000 of 1 GeV in 1024 slots 1989 and 457: no size at
+// which the masked kernels are the faster ones.  (The other policies, and no policy by tuning,
+// ask for their own kernels, deterministic appends for a fixed order,
+// parent-slot reuse for its own placement, and a profile of the kernels of an
+// iteration for those kernels.)
+bool local_steps(const ems_ctx* c)
+{
+    const uint32_t own = (1u << R_VAC) | (1u << R_INIT) | (1u << R_DRAIN);
+    const bool fused = c->policy == EMS_SORT_PARTITION && c->fuse_interactions && c->fuse_along;
+    const bool untuned = c->policy == EMS_SORT_NONE && !c->tuned;
+    return (fused || untuned) && !c->reuse_parent && !c->opt.deterministic && !(c->prof_mask & ~own) && steps_fit(c);
+}
+
 template <class R, bool STAGED>
 auto steps_kernel(bool field)
 {
@@ -785,7 +804,7 @@ void launch_steps(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool
     }
     ln.one(R_DRAIN, staged ? steps_kernel<R, true>(d.has_field) : steps_kernel<R, false>(d.has_field),
            dim3(sh.blocks), dim3(kStepsThreads), lds, st, d, (Initializer*)(c->ws + c->L.drain_stack),
-           c->L.stack_records / sh.blocks, sh.per_block, n_iter, sync ? 1 : 0, tail ? 1 : 0);
+           c->L.stack_records / sh.blocks, sh.per_block, n_iter, sync ? 1 : 0, tail ? 1 : 0, tail && !local_steps(c) ? 1 : 0);
 }
 
 void launch_steps_any(ems_ctx* c, uint32_t n_iter, uint32_t n_count, bool sync, bool tail)
@@ -801,25 +820,6 @@ void launch_drain(ems_ctx* c)
 {
     const uint64_t rounds = (uint64_t)c->drain_steps * (kDrainBurst * kStepRounds);
     launch_steps_any(c, (uint32_t)std::min<uint64_t>(rounds, UINT32_MAX), 1, false, true);
-}
-
-// Step iterations run as block-local step loops: where every launch is fused
-// and slots are partitioned by action, and where the caller left the schedule
-// to the library (no policy, no tuning; the tracks' results are the same
-// under every schedule).  With the default options, masked kernels on four
-// streams against the loops, a whole call: 500 electrons of 1 GeV in 2^17
-// slots 35.9 and 6.4 ms, one of 10 MeV 8.4 and 0.53, 5000 of 1 GeV in 2^20
-// slots 70.0 and 11.2, 2000 of 1 GeV in 1024 slots 1989 and 457: no size at
-// which the masked kernels are the faster ones.  (The other policies, and no policy by tuning,
-// ask for their own kernels, deterministic appends for a fixed order,
-// parent-slot reuse for its own placement, and a profile of the kernels of an
-// iteration for those kernels.)
-bool local_steps(const ems_ctx* c)
-{
-    const uint32_t own = (1u << R_VAC) | (1u << R_INIT) | (1u << R_DRAIN);
-    const bool fused = c->policy == EMS_SORT_PARTITION && c->fuse_interactions && c->fuse_along;
-    const bool untuned = c->policy == EMS_SORT_NONE && !c->tuned;
-    return (fused || untuned) && !c->reuse_parent && !c->opt.deterministic && !(c->prof_mask & ~own) && steps_fit(c);
 }
 
 // Record the events whose rows emptied in the iterations launched so far.

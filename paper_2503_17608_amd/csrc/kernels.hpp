@@ -2001,7 +2001,7 @@ constexpr size_t steps_lds(uint32_t slots, size_t tables) { return (tables + 15)
 // if so, else by role.
 template <class R, bool FIELD, bool STAGED>
 __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* stack, uint32_t stack_cap,
-                                                         uint32_t per_block, uint32_t n_iter, int sync, int tail)
+                                                         uint32_t per_block, uint32_t n_iter, int sync, int tail, int dealt)
 {
     extern __shared__ __align__(16) unsigned char ems_lds[];
     // by the round's parity: slots per list, places of the lists given out,
@@ -2024,12 +2024,15 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
     // (then the block's tallies, at tally_lds)
     const uint32_t nt = blockDim.x, tid = threadIdx.x, nw = nt / 64;
     const int lane = lane_id();
-    // A block's slots: a contiguous range, or in a drain every gridDim'th 64
-    // slots.  The tracks that a drain finds are where the separate kernels left
+    // A block's slots: a contiguous range, or `dealt` out, every gridDim'th 64
+    // slots.  A drain after separate kernels finds the tracks where those left
     // them, charged ones low in the slot array and neutral ones high, so that
     // ranges would hold very different numbers of them (radix policy, 10^4 x
-    // 1 GeV in 2^20 slots, drain below 65536: 26.8 ms with ranges, 24.6 so).
-    const uint32_t slot0 = blockIdx.x * (tail ? 64u : per_block), row_step = tail ? 64u * gridDim.x : 64u;
+    // 1 GeV in 2^20 slots, drain below 65536: 26.8 ms with ranges, 24.6 dealt
+    // out).  After these loops the ranges hold alike, and the rows of a range
+    // lie together (16 events of up to 100 GeV in 2^22 slots: 62.8 ms with
+    // ranges, 66.3 dealt out).
+    const uint32_t slot0 = blockIdx.x * (dealt ? 64u : per_block), row_step = dealt ? 64u * gridDim.x : 64u;
     auto slot_of = [&](uint32_t l) { return slot0 + (l >> 6) * row_step + (l & 63u); };
     if (tid < 32) (&cnt[0][0])[tid] = (&listed[0][0])[tid] = 0;
     if (tid < T_NUM) tot[tid] = 0;
