@@ -441,21 +441,24 @@ __global__ void k_ledger_sum(const Ledger* led, uint32_t n_rep, uint32_t ledger_
 }
 
 // Deposits [n][n_slabs] and ledgers [n] of the rows rows[0, n), summed over
-// their copies in copy order, into host memory the device can write: block b
-// takes row b.  (Written straight over the bus: a copy of the device's sums
-// and its completion would follow the kernel otherwise, 25 us for one event.)
+// their copies in copy order, into host memory the device can write: block
+// (b, c) takes every gridDim.y'th blockDim slabs of row b from c on.  (Written
+// straight over the bus: a copy of the device's sums and its completion would
+// follow the kernel otherwise, 25 us for one event.  A block per row took 126
+// us for one event of 2000 slabs and 2.1 ms for 65534, bound by the latency
+// of its 128 threads' reads and writes; so 30 and 40 us.)
 __global__ void k_read_rows(const uint32_t* rows, const double* edep, uint32_t n_rep_e, uint64_t edep_rs,
                             uint32_t stride, uint32_t n_slabs, const Ledger* led, uint32_t n_rep, uint32_t ledger_rs,
                             double* edep_out, Ledger* led_out)
 {
     const uint32_t row = rows[blockIdx.x];
     if (edep_out)
-        for (uint32_t j = threadIdx.x; j < n_slabs; j += blockDim.x) {
+        for (uint32_t j = blockIdx.y * blockDim.x + threadIdx.x; j < n_slabs; j += gridDim.y * blockDim.x) {
             double v = 0.0;
             for (uint32_t r = 0; r < n_rep_e; ++r) v += edep[r * edep_rs + (uint64_t)row * stride + j];
             edep_out[(uint64_t)blockIdx.x * n_slabs + j] = v;
         }
-    if (led_out && threadIdx.x == 0) {
+    if (led_out && blockIdx.y == 0 && threadIdx.x == 0) {
         Ledger s{};
         for (uint32_t r = 0; r < n_rep; ++r) {
             const Ledger& l = led[(size_t)r * ledger_rs + row];
@@ -1583,7 +1586,9 @@ static ems_status read_rows(ems_ctx* c, const uint32_t* rows, uint64_t n, double
         const uint64_t k = std::min(n - done, fit);
         char* buf = (char*)c->staging + h * half;
         std::memcpy(buf, rows + done, 4 * k);
-        hipLaunchKernelGGL(k_read_rows, dim3((uint32_t)k), dim3(128), 0, c->stream, (const uint32_t*)buf,
+        // few rows: several blocks each, up to four a CU in all
+        const uint32_t split = std::max(1u, std::min((ns + 127) / 128, (uint32_t)(1024 / k)));
+        hipLaunchKernelGGL(k_read_rows, dim3((uint32_t)k, split), dim3(128), 0, c->stream, (const uint32_t*)buf,
                            (const double*)(c->ws + c->L.edep), c->L.n_rep_e, c->L.edep_rs, (uint32_t)c->opt.max_slabs,
                            ns, (const Ledger*)(c->ws + c->L.ledger), c->L.n_rep, c->L.ledger_rs,
                            edep ? (double*)(buf + at_edep) : nullptr, ledgers ? (Ledger*)(buf + at_led) : nullptr);

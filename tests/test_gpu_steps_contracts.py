@@ -327,3 +327,28 @@ def test_a_cleared_tuning_leaves_the_schedule_to_the_library():
     s.clear_tuning()
     assert s.tuning() == new and loops()
     s.close()
+
+
+@pytest.mark.parametrize("n_slabs,n_events", [(1, 3), (127, 1), (129, 5), (2000, 1), (65534, 5)])
+def test_events_of_wide_stacks_are_read_whole(n_slabs, n_events):
+    """Rows of one to 65534 slabs (several blocks per row; four rows fill half of the staging buffer)."""
+    from paper_2503_17608_amd import emstep
+    s = emstep.Session(4096, max_events=n_events, max_slabs=n_slabs, max_materials=1, streams=1)
+    s.load(np.arange(n_slabs + 1) * (70.0 / n_slabs), np.zeros(n_slabs, np.int32), 20.0, (1.0, 0.0, 0.0),
+           [workloads.LEAD], 0.1)
+    p = np.zeros(8 * n_events, dtype=emstep.PRIMARY_DTYPE)
+    p["event"], p["key"], p["type"], p["T"] = np.arange(len(p)) % n_events, np.arange(len(p)), 1, 5.0
+    p["u"][:, 2] = 1.0
+    p["slab"] = np.linspace(0, n_slabs - 1, len(p)).astype(np.int32)
+    p["r"][:, 2] = (p["slab"] + 0.5) * (70.0 / n_slabs)
+    s.push(p)
+    s.run()
+    e_all, l_all, ev_all = s.read_all()
+    ids = np.arange(n_events)[::-1]
+    rows = [list(ev_all).index(i) for i in ids]
+    edep, led = s.tallies_by_event(ids)
+    assert edep.tobytes() == e_all[rows].tobytes() and led.tobytes() == l_all[rows].tobytes()
+    assert np.all(edep.max(1) > 0) and (edep[:, -1] > 0).any() and (edep[:, 0] > 0).any()
+    one_e, one_l = s.read_edep(0)
+    assert one_e.tobytes() == edep[-1].tobytes() and one_l.tobytes() == led[-1].tobytes()
+    s.close()
