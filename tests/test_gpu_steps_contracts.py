@@ -8,7 +8,8 @@ import torch
 
 import workloads
 from paper_2503_17608_amd import multistream
-from tests.gpu_helpers import assert_events_match, assert_same_as, run_oracle, session_for
+from tests.gpu_helpers import (assert_events_match, assert_same_as, random_states, run_oracle, session_for,
+                               to_lib_tracks)
 
 pytestmark = pytest.mark.gpu
 
@@ -351,4 +352,61 @@ def test_events_of_wide_stacks_are_read_whole(n_slabs, n_events):
     assert np.all(edep.max(1) > 0) and (edep[:, -1] > 0).any() and (edep[:, 0] > 0).any()
     one_e, one_l = s.read_edep(0)
     assert one_e.tobytes() == edep[-1].tobytes() and one_l.tobytes() == led[-1].tobytes()
+    s.close()
+
+
+def _after(w, states, slots, precision, max_events, iterations, local):
+    """Tracks by key, ledgers and deposits after `iterations` of the loops in one launch, or of separate kernels."""
+    s = session_for(w, n_slots=slots, precision=precision, max_events=max_events, n_initializers=4 * len(states),
+                    **LOCAL)
+    rows = np.array([s.register_event(10 + i) for i in range(4)], dtype=np.uint32)
+    t = to_lib_tracks(states, rows[np.arange(len(states)) % 4])
+    t["type"][np.arange(len(t)) % 60 != 0] = -1      # 5 of a block's 274 slots: none of its tracks has to wait
+    s.inject(t)
+    s.set_tuning(fuse_interactions=True)
+    if local:
+        s.step(iterations)
+    else:
+        s.iterate(iterations)
+    t = s.read_tracks(slots)
+    t = np.concatenate([t[t["type"] >= 0], s.read_secondaries()])
+    edep, led = s.tallies_by_event(np.arange(10, 14))
+    s.close()
+    return t[np.argsort(t["key"], kind="stable")], edep, led
+
+
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+@pytest.mark.parametrize("max_events,iterations", [(4, 1), (4, 7), (2000, 7)])    # 4 rows fit a block's LDS, 2000 do not
+def test_iterations_in_one_launch_equal_the_separate_kernels(precision, max_events, iterations):
+    """Seven iterations in step: tracks bit for bit, whole numbers equal; deposits and escapes are sums of at most
+    10^5 terms in another order, each rounded to 1.1e-16."""
+    w = _electrons(1, 1000.0)
+    states = random_states(w, 60000, np.random.default_rng(iterations), f32=precision == "mixed")
+    ref, e_ref, l_ref = _after(w, states, 70001, precision, max_events, iterations, False)
+    t, edep, led = _after(w, states, 70001, precision, max_events, iterations, True)
+    assert len(t) == len(ref)
+    for f in t.dtype.names:
+        if f != "row":
+            assert np.ascontiguousarray(t[f]).tobytes() == np.ascontiguousarray(ref[f]).tobytes(), f
+    for f in led.dtype.names:
+        if f != "escaped":
+            assert np.array_equal(led[f], l_ref[f]), f
+    assert np.all(np.abs(edep - e_ref) <= 1.2e-11 * e_ref) and edep.sum() > 0
+    assert np.all(np.abs(led["escaped"] - l_ref["escaped"]) <= 1.2e-11 * l_ref["escaped"])
+
+
+@pytest.mark.parametrize("policy", ["partition", "radix"])
+def test_phase_tables_with_separate_kernels(policy):
+    """Masked and sorted iterations in one run (sort points off in some occupancy buckets), interactions apart so
+    that they run as separate kernels."""
+    w = _electrons(20, 1000.0)
+    e_ref, l_ref, steps = run_oracle(w)
+    s = session_for(w, n_slots=1 << 14, sort_policy=policy, graph_iterations=4, streams=1)
+    for masks in ((0, 0xFFFFFFFF), (0xFFFFFFFF, 0), (0x0000003F, 0xFFFFFFC0), (0x00000FC0, 0x000001FF)):
+        s.set_tuning(phase_sort=masks, fuse_interactions=False)
+        s.push(w.primaries)
+        s.run()
+        edep, led = s.tallies_by_event(np.arange(w.n_events))
+        s.release(np.arange(w.n_events, dtype=np.uint64))
+        assert_events_match(w, edep, led, e_ref, l_ref, (policy, masks))
     s.close()
