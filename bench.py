@@ -763,7 +763,8 @@ def main():
         key = {"workload": w.name, "precision": precision, "n_slots": w.n_slots, "sort_policy": args.policy,
                "init_partition": args.init_partition, "max_substeps": args.max_substeps,
                "drain_threshold": args.drain_threshold, "reuse_parent_slot": args.reuse_parent_slot,
-               "fuse_interactions": args.fuse_interactions, "fuse_along": int(both),
+               "fuse_interactions": args.fuse_interactions,
+               "fuse_along": args.fuse_along if prof_kernel == "steps" else int(both),
                "phase_sort": ["0x%08X" % m for m in args.phase_sort]}
         label = "along_both" if both else prof_kernel
         t = committed_traffic(label, key)

@@ -114,7 +114,7 @@ typedef struct {
                                   launch overhead of the outer loop) */
     int32_t lds_tables;        /* 1: each block of the along-step kernels (which run the pre-step)
                                   stages the physics tables in LDS; 0: tables are read through the
-                                  caches (the block-local step loops always stage them) */
+                                  caches (the block-local step loops stage them wherever they fit) */
     int32_t streams;           /* 1..4: independent kernels of an iteration (the along-step kernels;
                                   the interaction kernels) run as concurrent branches on up to this
                                   many default-priority streams created by the library (paper:

@@ -846,6 +846,7 @@ __device__ __forceinline__ uint32_t reuse_slot(const Dev<R>& d, uint32_t s, SecB
     return 1u;
 }
 
+// ---- pre-step: interaction length, physics step limit -------------------------------
 // Pre-step of one live, non-paused track, in registers (the caller loaded
 // its fields once and stores what persists once): draws the interaction
 // length when it is unset, and gives the total cross section, the physics
@@ -887,7 +888,6 @@ __device__ __forceinline__ void pre_step(const Dev<R>& d, const Tables<R>& tb, i
     s_phys = (double)sp;
 }
 
-// ---- pre-step: interaction length, physics step limit, along-step action -----------
 // ---- geometry helpers -----------------------------------------------------------
 __device__ __forceinline__ double face_plane(const double* zp, int slab, double W, int face)
 {
@@ -1858,8 +1858,9 @@ __global__ void __launch_bounds__(kStepMaxBlock) k_interact_all(Dev<R> d)
 
 // ---- block-local step loops -----------------------------------------------------
 // One launch runs several step iterations: each block owns a share of the
-// track slots and steps their tracks by itself, so that an iteration needs no launches, no global scan of
-// vacancies, no sort of the slots and no trip through the initializer buffer.
+// track slots and steps their tracks by itself, so that an iteration needs no
+// launches, no global scan of vacancies, no sort of the slots and no trip
+// through the initializer buffer.
 //
 // A step is cut into the parts below, and every slot has a state byte in LDS:
 // its particle type and the part its track waits for.  The block works in
