@@ -413,9 +413,10 @@ ems_status ems_sort_keys_noalloc(ems_ctx* ctx, const uint8_t* keys, uint64_t n, 
  * fit the blocks' LDS.  A launch of ems_step is up to 32 iterations (or
  * graph_iterations, if more).  The initializer buffer and the pending
  * primaries fill vacant slots between launches; within one, secondaries take
- * vacant slots of their block or wait, if it has none or holds more than 1.25
- * times the blocks' average of tracks plus 128.  The sort points, block sizes, graph batches and worker
- * streams then play no part.  The results are those of the separate kernels.
+ * vacant slots of their block or wait, if it has none or holds more than a
+ * sixteenth (ems_run: a quarter) above the blocks' average of tracks plus
+ * 128.  The sort points, block sizes, graph batches and worker streams then
+ * play no part.  The results are those of the separate kernels.
  *
  * Drain (ems_run only; 0 = off): once the latest counter snapshot shows fewer
  * than drain_threshold tracks alive, queued or pending, and no more than the

@@ -2053,13 +2053,18 @@ __global__ void __launch_bounds__(kStepsThreads) k_steps(Dev<R> d, Initializer* 
         state[l] = st;
     }
     // Tracks of a block above a quarter more than the blocks' average wait for
-    // the next fill.  (The average from words that only the vacancy pass
+    // the next fill; where tracks step in iterations, and every block waits in
+    // each for its slowest part, above a sixteenth more.  (FP64 serving at 2^23
+    // slots, p50 / p99 in ms at 452 and 520 events/s: a quarter 132 / 243 and
+    // 218 / 362, a sixteenth 112 / 199 and 172 / 292, separate kernels 118 /
+    // 217 and 182 / 297; no limit 311 / 381 and 330 / 399.)
+    // The average comes from words that only the vacancy pass
     // writes: all waves of a block must place by the same number, and n_alive
-    // changes while blocks of this launch end.)
+    // changes while blocks of this launch end.
     const Counters* ctr = d.ctr;
     const uint32_t share = (uint32_t)(((unsigned long long)ctr->alive_before + ctr->n_take_q + ctr->n_take_p +
                                        ctr->q_base) / gridDim.x);
-    const uint32_t most = share + share / 4 + 128;
+    const uint32_t most = share + share / (sync ? 16 : 4) + 128;
     Initializer* bstack = stack + (size_t)blockIdx.x * stack_cap;
     uint32_t live0 = 0, live = 0, live_at_start = 0;
     uint32_t avail = 0;                      // vacancies secondaries may take this round
